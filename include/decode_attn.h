@@ -423,6 +423,45 @@ int da_decode_attn_scheduled(const void* q, const void* k, const void* v,
                              const da_schedule* sched, const void* meta_dev, void* workspace,
                              size_t workspace_bytes, void* stream);
 
+/* Decode attention over a batch of mixed lengths that only the device holds:
+ * the same result as da_decode_attn with cu_seqlens_k, or as
+ * da_decode_attn_paged, up to rounding order, in one launch that shares the
+ * batch's 32-key tiles evenly among the CUs instead of cutting every sequence
+ * into one number of chunks.  The workgroups read the lengths and find the
+ * deal themselves: each takes a run of consecutive tiles of the batch, which
+ * may end one sequence, hold others and begin the next; sequences that two or
+ * more workgroups share are merged inside the launch.  No length is read on
+ * the host, nothing is allocated, the call can be captured, and replays follow
+ * the lengths the device then holds (each at most L_K_max).  Results are
+ * bit-identical across runs for the same lengths.
+ *   block_table == NULL: k, v packed as for da_decode_attn with cu_seqlens_k
+ *     (page_size, max_pages, num_pages, seq_lens ignored); otherwise paged as
+ *     for da_decode_attn_paged (cu_seqlens_k ignored)
+ *   keys       keys of the whole batch or an upper bound, if the host knows
+ *              one (packed: the rows of k); <= 0 otherwise.  It picks the
+ *              cache hint, never the result
+ *   workspace  >= da_dealt_workspace_bytes(B, H_Q, H_KV, 0): chunk states and
+ *              the counter region, zero before the first call as for
+ *              da_decode_attn; every call leaves it zero
+ * Other arguments and errors as for da_decode_attn and da_decode_attn_paged;
+ * DA_ERR_NULL without cu_seqlens_k or a block table, DA_ERR_ARG for a shape
+ * with more than DA_ARRIVAL_BYTES / DA_ARRIVAL_STRIDE (sequence, head tile)
+ * pairs or whose head tiles would leave more than a tenth of the CUs idle. */
+int da_decode_attn_dealt(const void* q, const void* k, const void* v, const int32_t* cu_seqlens_k,
+                         const int32_t* block_table, const int32_t* seq_lens, int page_size, int max_pages,
+                         int num_pages, void* out, float* lse_out, int B, int H_Q, int H_KV, int L_K_max, int d,
+                         float softmax_scale, int64_t keys, void* workspace, size_t workspace_bytes,
+                         void* stream);
+
+/* Workspace bytes da_decode_attn_dealt needs for this shape (num_cus 0: query
+ * the current device); 0 for a shape it does not take. */
+size_t da_dealt_workspace_bytes(int B, int H_Q, int H_KV, int num_cus);
+
+/* 1 where da_decode_attn_dealt is expected to beat the launch with one split
+ * count for all sequences (measured lines on the keys per CU and the longest
+ * sequence), else 0.  keys and num_cus as above.  Host only. */
+int da_prefers_dealt(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int num_cus);
+
 /* The split step alone: the partial softmax state of every chunk (the
  * per-chunk max, sum and unnormalised output the paper's final reduction
  * merges; Sections 3.1, 5.3).  Same inputs as da_decode_attn; num_splits

@@ -19,6 +19,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libdecode_attn.so")
 HEAD_DIM = 128
 MAX_SPLITS = 64
+DEALT_MIN_KEYS = 1505  # da_prefers_dealt never holds for shorter batches: no need to ask
 
 DA_OK = 0
 DA_ERR_NULL = -1
@@ -42,7 +43,8 @@ EXPORTS = (
     "da_choose_splits", "da_model_time", "da_make_plan", "da_workspace_bytes", "da_split_bounds", "da_decode_attn",
     "da_decode_attn_planned", "da_decode_attn_noalloc", "da_decode_attn_paged", "da_decode_attn_paged_planned", "da_schedule_max_bytes",
     "da_make_schedule", "da_schedule_workspace_bytes",
-    "da_decode_attn_scheduled", "da_split_partials", "da_combine_splits", "da_device_info", "da_strerror",
+    "da_decode_attn_scheduled", "da_decode_attn_dealt", "da_dealt_workspace_bytes", "da_prefers_dealt",
+    "da_split_partials", "da_combine_splits", "da_device_info", "da_strerror",
     "da_last_error",
 )
 
@@ -147,6 +149,13 @@ def load() -> ctypes.CDLL:
     lib.da_decode_attn_scheduled.argtypes = [_P, _P, _P, _P, _P, _P, _I, _I, _I, _P, _P, _I, _F,
                                              ctypes.POINTER(DaSchedule), _P, _P, _Z, _P]
     lib.da_decode_attn_scheduled.restype = _I
+    lib.da_dealt_workspace_bytes.argtypes = [_I, _I, _I, _I]
+    lib.da_dealt_workspace_bytes.restype = _Z
+    lib.da_prefers_dealt.argtypes = [_I, _I, _I, _I, ctypes.c_int64, _I]
+    lib.da_prefers_dealt.restype = _I
+    lib.da_decode_attn_dealt.argtypes = [_P, _P, _P, _P, _P, _P, _I, _I, _I, _P, _P, _I, _I, _I, _I, _I, _F,
+                                         ctypes.c_int64, _P, _Z, _P]
+    lib.da_decode_attn_dealt.restype = _I
     lib.da_split_partials.argtypes = [_P, _P, _P, _P, _P, _P, _P, _I, _I, _I, _I, _I, _F, _I, _I, _P]
     lib.da_split_partials.restype = _I
     lib.da_combine_splits.argtypes = [_P, _P, _P, _P, _P, _I, _I, _I, _I, _P]
@@ -206,6 +215,14 @@ def da_make_plan(B: int, H_Q: int, H_KV: int, L_K_max: int, d: int = HEAD_DIM, n
 
 def da_workspace_bytes(B: int, H_Q: int, d: int, num_splits: int) -> int:
     return int(load().da_workspace_bytes(B, H_Q, d, num_splits))
+
+
+def da_dealt_workspace_bytes(B: int, H_Q: int, H_KV: int, num_cus: int = 0) -> int:
+    return int(load().da_dealt_workspace_bytes(B, H_Q, H_KV, num_cus))
+
+
+def da_prefers_dealt(B: int, H_Q: int, H_KV: int, L_K_max: int, keys: int = 0, num_cus: int = 0) -> bool:
+    return bool(load().da_prefers_dealt(B, H_Q, H_KV, L_K_max, keys, num_cus))
 
 
 def da_split_bounds(L: int, num_splits: int) -> List[int]:
@@ -275,6 +292,10 @@ def workspace_for(dev: torch.device, stream_handle: int, nbytes: int) -> torch.T
             _retired.append(ws)
         ws = torch.zeros(max(nbytes, 256), dtype=torch.uint8, device=dev)
         _workspaces[key] = ws
+        if dev.type == "cuda" and stream_handle != torch.cuda.current_stream(dev).cuda_stream:
+            # the fill runs on torch's current stream: the call's own stream waits for it
+            own = torch.cuda.ExternalStream(stream_handle, device=dev) if stream_handle else torch.cuda.default_stream(dev)
+            own.wait_stream(torch.cuda.current_stream(dev))
     return ws
 
 
@@ -282,8 +303,13 @@ def da_decode_attn(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, cu_seqlens
                    out: Optional[torch.Tensor] = None, lse_out: Optional[torch.Tensor] = None, *,
                    L_K_max: Optional[int] = None, softmax_scale: float = 0.0, num_splits: int = 0,
                    pack_gqa: int = -1, workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
-    """O = softmax(scale q K^T) V for one decode step; returns `out`."""
+    """O = softmax(scale q K^T) V for one decode step; returns `out`.  A packed
+    batch with nothing forced goes to da_decode_attn_dealt where that pays."""
     B, H_Q, H_KV, L, d = _shapes(q, k, v, cu_seqlens_k, L_K_max)
+    if (cu_seqlens_k is not None and workspace is None and num_splits <= 0 and pack_gqa == -1
+            and L >= DEALT_MIN_KEYS and d == HEAD_DIM and load().da_prefers_dealt(B, H_Q, H_KV, L, k.shape[0], 0)):
+        return da_decode_attn_dealt(q, k, v, L, cu_seqlens_k, out=out, lse_out=lse_out, softmax_scale=softmax_scale,
+                                    stream=stream)
     dev = q.device
     if out is None:
         out = torch.empty((B, H_Q, d), dtype=torch.bfloat16, device=dev)
@@ -365,8 +391,13 @@ def da_decode_attn_paged(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.
                          pack_gqa: int = -1, workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """Decode attention over a paged KV cache; returns `out`.
     k_cache, v_cache: [num_pages, page_size, H_KV, d] bf16; block_table: [B, max_pages] int32;
-    seq_lens: [B] int32; L_K_max: host-known longest sequence."""
+    seq_lens: [B] int32; L_K_max: host-known longest sequence.  A batch with
+    nothing forced goes to da_decode_attn_dealt where that pays."""
     B, H_Q, H_KV, d, page_size, max_pages, num_pages = _paged_args(q, k_cache, v_cache, block_table, seq_lens)
+    if (workspace is None and num_splits <= 0 and pack_gqa == -1 and L_K_max >= DEALT_MIN_KEYS and d == HEAD_DIM
+            and load().da_prefers_dealt(B, H_Q, H_KV, int(L_K_max), 0, 0)):
+        return da_decode_attn_dealt(q, k_cache, v_cache, int(L_K_max), None, block_table, seq_lens, out, lse_out,
+                                    softmax_scale=softmax_scale, stream=stream)
     dev = q.device
     if out is None:
         out = torch.empty((B, H_Q, d), dtype=torch.bfloat16, device=dev)
@@ -472,6 +503,38 @@ def da_decode_attn_scheduled(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, 
                                            _ptr(seq_lens), page_size, max_pages, num_pages, _ptr(out),
                                            _ptr(lse_out), d, float(softmax_scale), ctypes.byref(sched),
                                            _ptr(meta_dev), _ptr(workspace), ws_bytes, s_handle))
+    return out
+
+
+def da_decode_attn_dealt(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, L_K_max: int,
+                         cu_seqlens_k: Optional[torch.Tensor] = None, block_table: Optional[torch.Tensor] = None,
+                         seq_lens: Optional[torch.Tensor] = None, out: Optional[torch.Tensor] = None,
+                         lse_out: Optional[torch.Tensor] = None, *, softmax_scale: float = 0.0,
+                         workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
+    """Decode attention over a batch of mixed lengths, its tiles shared evenly
+    among the CUs on the device; returns `out`.  Packed K/V with cu_seqlens_k
+    when block_table is None, else paged.  da_decode_attn and
+    da_decode_attn_paged come here by themselves where it pays."""
+    page_size = max_pages = num_pages = keys = 0
+    if block_table is None:
+        if cu_seqlens_k is None:
+            raise ValueError("cu_seqlens_k, or block_table and seq_lens, are required")
+        B, H_Q, H_KV, L, d = _shapes(q, k, v, cu_seqlens_k, L_K_max)
+        keys = k.shape[0]
+    else:
+        B, H_Q, H_KV, d, page_size, max_pages, num_pages = _paged_args(q, k, v, block_table, seq_lens)
+        L = int(L_K_max)
+    dev = q.device
+    if out is None:
+        out = torch.empty((B, H_Q, d), dtype=torch.bfloat16, device=dev)
+    s_handle = _stream(dev, stream)
+    if workspace is None:
+        workspace = workspace_for(dev, s_handle, da_dealt_workspace_bytes(B, H_Q, H_KV))
+    ws_bytes = workspace.numel() * workspace.element_size()
+    _check(load().da_decode_attn_dealt(_ptr(q), _ptr(k), _ptr(v), _ptr(cu_seqlens_k), _ptr(block_table),
+                                       _ptr(seq_lens), page_size, max_pages, num_pages, _ptr(out), _ptr(lse_out),
+                                       B, H_Q, H_KV, L, d, float(softmax_scale), keys, _ptr(workspace), ws_bytes,
+                                       s_handle))
     return out
 
 

@@ -153,6 +153,7 @@ struct Params {
   const int32_t* work;  // nullable: per-sequence schedule, int32x4 {tile, first, end, state row} per workgroup
   const int32_t* seqs;  // schedule, kFused: int32x2 [B] {first chunk-state row or -1, chunk count}
   int state_rows;       // chunk-state rows of the schedule
+  int groups;           // dealt launch: workgroups per head tile
   int B, H_Q, H_KV, L_K, g, hpt, tiles_per_seq, tiles, s, mode;
   int xcd_group;        // 1: consecutive tiles share an XCD (packing off)
   Div div_s, div_tps, div_g;  // s, tiles_per_seq, g
@@ -295,21 +296,20 @@ __device__ __forceinline__ void merge_rows(const float* o_part, const float* m_p
 // s chunk states for its hpt <= 32 rows (query heads), with every thread
 // holding float4 output columns.  Chunk i of the tile's head h is state row
 // srow0 + i * cstride + h (state_rows rows in all); its output row is orow0
-// + h.  The states were written in this launch by
+// + h; with FIRST, chunk 0 sits first_rows further on.  The states were written in this launch by
 // other workgroups with device-scope stores and are read with device-scope
 // loads.  Per output element the operations and their order are those of
 // merge_rows (maximum over non-empty chunks, then the weights, L and O
 // accumulated in chunk order), so both merges give the same bits.  The
 // code is kept short and rolled: it runs once per tile, on cold
 // instruction caches.  `lds` holds at least 3 x 64 x 32 floats.
-template <int NT, int W>
+template <int NT, int W, bool FIRST = false>
 __device__ __forceinline__ void merge_tile(const Params& p, float* lds, int64_t srow0, int64_t cstride, int s,
-                                           int64_t orow0, int64_t state_rows, int tid) {
+                                           int64_t orow0, int64_t state_rows, int tid, uint32_t first_rows = 0) {
   constexpr int T = 64 * W;              // threads
   constexpr int R = T / 32;              // thread t stages row t % 32 of chunks t / 32 + R u
   constexpr int IPT = NT * 16 * 32 / T;  // float4 columns per thread (hpt * 32 items over T threads)
-  constexpr int CB = 16 / IPT;           // chunks of columns loaded at once
-  static_assert(CB == da::kFusedBatch[NT - 1], "the planner prices the merge in batches of CB chunks");
+  constexpr int CB = da::kFusedBatch[NT - 1];  // chunks of columns loaded at once
   constexpr uint32_t kOut = 0xfffffff0u; // an offset past every buffer: reads zero, touches nothing
   const int hpt = p.hpt;
   // 32-bit offsets: the chunk states of a call stay below 2 GiB (checked on the host), and the
@@ -342,7 +342,11 @@ __device__ __forceinline__ void merge_tile(const Params& p, float* lds, int64_t 
         if (T * j < items && i0 + u < s)  // uniform
         a[j][u] = __builtin_bit_cast(
             f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                       ors, ooff[j] != kOut ? ooff[j] + (uint32_t)(i0 + u) * ostride : kOut, 0, kDeviceScope));
+                       ors,
+                       ooff[j] != kOut
+                           ? ooff[j] + (uint32_t)(i0 + u) * ostride + (FIRST && i0 + u == 0 ? first_rows * D * 4u : 0u)
+                           : kOut,
+                       0, kDeviceScope));
   };
   auto store_item = [&](int j, float M, float L, const f32x4& o) {
     const int item = tid + T * j, h = item >> 5, c = item & 31;
@@ -364,7 +368,8 @@ __device__ __forceinline__ void merge_tile(const Params& p, float* lds, int64_t 
       const uint32_t moff = h < (uint32_t)hpt ? (r0 + h) * 4u : kOut;
 #pragma unroll
       for (int u = 0; u < CB; ++u) {  // chunks past s read as l = 0, never live
-        const uint32_t off = moff != kOut && u < s ? moff + (uint32_t)u * rows * 4u : kOut;
+        const uint32_t off =
+            moff != kOut && u < s ? moff + (uint32_t)u * rows * 4u + (FIRST && u == 0 ? first_rows * 4u : 0u) : kOut;
         bm[j][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(mrs, off, 0, kDeviceScope));
         bl[j][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(lrs, off, 0, kDeviceScope));
       }
@@ -399,7 +404,8 @@ __device__ __forceinline__ void merge_tile(const Params& p, float* lds, int64_t 
     for (int u = 0; u < DA_MAX_SPLITS / R; ++u) {
       if (R * u >= s) break;  // uniform
       const int i = i0 + R * u;
-      const uint32_t off = moff != kOut && i < s ? moff + (uint32_t)i * rows * 4u : kOut;
+      const uint32_t off =
+          moff != kOut && i < s ? moff + (uint32_t)i * rows * 4u + (FIRST && i == 0 ? first_rows * 4u : 0u) : kOut;
       mv[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(mrs, off, 0, kDeviceScope));
       lv[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(lrs, off, 0, kDeviceScope));
     }
@@ -459,6 +465,275 @@ __device__ __forceinline__ void merge_tile(const Params& p, float* lds, int64_t 
   }
 #pragma unroll
   for (int j = 0; j < IPT; ++j) store_item(j, M[j], L[j], o[j]);
+}
+
+// One wave's running state over the 32-key tiles of a chunk: the packed query
+// heads as the MFMA B operand and, per 16-head column tile, the online
+// softmax's max and row-summed l and NB 16-dim blocks of unnormalised output.
+template <int NT, int NB>
+struct TileReducer {
+  bf16x8 q[NT][4];
+  float m[NT], l[NT];
+  f32x4 o[NT][NB];
+  float scale_log2;
+  int quad;
+
+  // Q^T as the MFMA B operand.  The reduction index of the product may
+  // map to head dims in any order as long as K and Q agree: k-step j,
+  // lane group `quad` covers dims [32j + 8*quad, +8).  The lane holds those
+  // dims of head column `col` (zeros for padding) of the hpt rows at qrow.
+  __device__ __forceinline__ void load_q(const uint16_t* qrow, int hpt, int col) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const int h = nt * 16 + col;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        u32x4 x = {0u, 0u, 0u, 0u};
+        if (h < hpt) x = *reinterpret_cast<const u32x4*>(qrow + (int64_t)h * D + 32 * j + 8 * quad);
+        q[nt][j] = as_bf16x8(x);
+      }
+    }
+  }
+
+  __device__ __forceinline__ void reset() {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      m[nt] = -INFINITY;
+      l[nt] = 0.f;
+#pragma unroll
+      for (int nn = 0; nn < NB; ++nn) o[nt][nn] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  }
+
+  // S^T[16 keys x 16 heads] per (mt, nt) from the tile's 8 K operands.
+  __device__ __forceinline__ void scores(const bf16x8 (&kop)[2][4], f32x4 (&sc)[NT][2]) const {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[mt][j], q[nt][j], acc, 0, 0, 0);
+        sc[nt][mt] = acc;
+      }
+  }
+
+  // Online softmax per head column, in log2 units of the scaled score: the
+  // max is taken on raw scores (the scale is positive) and each exponent is
+  // one fma, raw * scale*log2(e) - running max.  `last`: only the final tile
+  // can be shorter than 32 keys and needs its scores masked.
+  template <typename Last>
+  __device__ __forceinline__ void softmax(const f32x4 (&sc)[NT][2], int nvalid, Last last, bf16x8 (&pb)[NT]) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      float x[8];
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float r = sc[nt][mt][i];
+          if constexpr (Last::value) r = (mt * 16 + quad * 4 + i) < nvalid ? r : -INFINITY;
+          x[mt * 4 + i] = r;
+        }
+      const float rmax = max_rows(fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])),
+                                        fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7]))));
+      const float m_new = fmaxf(m[nt], rmax * scale_log2);
+      const float alpha = __builtin_amdgcn_exp2f(m[nt] - m_new);
+      float psum = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        x[e] = __builtin_amdgcn_exp2f(fmaf(x[e], scale_log2, -m_new));
+        psum += x[e];
+      }
+      l[nt] = l[nt] * alpha + psum;
+      m[nt] = m_new;
+      // alpha == 1 exactly when the column max did not move: skip the
+      // multiply by one (a wave-uniform branch)
+      if (__any(alpha != 1.0f)) {
+#pragma unroll
+        for (int nn = 0; nn < NB; ++nn) o[nt][nn] *= alpha;
+      }
+      u32x4 pk;
+      pk.x = pack_bf16x2(x[0], x[1]);
+      pk.y = pack_bf16x2(x[2], x[3]);
+      pk.z = pack_bf16x2(x[4], x[5]);
+      pk.w = pack_bf16x2(x[6], x[7]);
+      pb[nt] = as_bf16x8(pk);
+    }
+  }
+
+  // O^T[16 dims x 16 heads] += V^T[16 dims x 32 keys] . P^T[32 keys x 16 heads]
+  // The k index 8*quad + 4*mt + i of the product stands for key
+  // 16*mt + 4*quad + i, matching the score layout.  The V^T operand comes
+  // from transposing LDS reads (ds_read_b64_tr_b16): within each 16-lane
+  // group, output lane j receives element j%4 of the 8-byte chunks that
+  // lanes 4k + j/4 point at, k = 0..3.  Lane (quad, 4k + m) therefore points
+  // at dims [16nn + 4m, +4) of key 16mt + 4quad + k -- vaddr(mt, nn) gives
+  // that address for the stage layout in use -- and lane (quad, col)
+  // receives V[16mt + 4quad + k][16nn + col] for k = 0..3.  All 16 reads are
+  // issued before the first product so their LDS latency is paid once per
+  // tile rather than once per 16 output dims.
+  // With direct-to-LDS loads in flight (`opaque`; vaddr then gives LDS byte
+  // offsets), the reads are written as inline assembly followed by an
+  // explicit wait: the compiler cannot tell that they touch the other stage
+  // and would otherwise drain every outstanding load before them.
+  template <typename Addr, typename Opaque>
+  __device__ __forceinline__ void pv(const bf16x8 (&pb)[NT], Addr vaddr, Opaque opaque) {
+    s16x4 vlo[NB], vhi[NB];
+    if constexpr (Opaque::value) {
+#pragma unroll
+      for (int nn = 0; nn < NB; ++nn) {
+        asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(vlo[nn]) : "v"((uint32_t)vaddr(0, nn)) : "memory");
+        asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(vhi[nn]) : "v"((uint32_t)vaddr(1, nn)) : "memory");
+      }
+      // The wait names every result as an operand it updates, so nothing
+      // that reads them can be scheduled before it.
+      if constexpr (NB == 8)
+        asm volatile("s_waitcnt lgkmcnt(0)"
+                     : "+v"(vlo[0]), "+v"(vlo[1]), "+v"(vlo[2]), "+v"(vlo[3]), "+v"(vlo[4]), "+v"(vlo[5]),
+                       "+v"(vlo[6]), "+v"(vlo[7]), "+v"(vhi[0]), "+v"(vhi[1]), "+v"(vhi[2]), "+v"(vhi[3]),
+                       "+v"(vhi[4]), "+v"(vhi[5]), "+v"(vhi[6]), "+v"(vhi[7])
+                     :
+                     : "memory");
+      else if constexpr (NB == 4)
+        asm volatile("s_waitcnt lgkmcnt(0)"
+                     : "+v"(vlo[0]), "+v"(vlo[1]), "+v"(vlo[2]), "+v"(vlo[3]), "+v"(vhi[0]), "+v"(vhi[1]),
+                       "+v"(vhi[2]), "+v"(vhi[3])
+                     :
+                     : "memory");
+      else
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(vlo[0]), "+v"(vlo[1]), "+v"(vhi[0]), "+v"(vhi[1]) : : "memory");
+    } else {
+#pragma unroll
+      for (int nn = 0; nn < NB; ++nn) {
+        vlo[nn] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)vaddr(0, nn));
+        vhi[nn] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)vaddr(1, nn));
+      }
+    }
+    __builtin_amdgcn_sched_group_barrier(0x100, 2 * NB, 0);   // the DS reads first
+    __builtin_amdgcn_sched_group_barrier(0x008, NB * NT, 0);  // then the MFMAs
+#pragma unroll
+    for (int nn = 0; nn < NB; ++nn) {
+      const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(vlo[nn], vhi[nn], 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+        o[nt][nn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pb[nt], o[nt][nn], 0, 0, 0);
+    }
+  }
+};
+
+// A chunk's W wave states are merged in one step.  Every wave publishes its
+// state (per head column: running max, row-summed l, NB x 4 output values;
+// all waves share one lane layout) to its LDS slot, value-major
+// ([value][lane], conflict-free).  After a barrier (the caller's), wave w
+// merges the W states for its NB/W blocks of 16 output dims -- maximum,
+// weights, then sums taken in wave order, so the result is the same on every
+// run -- and writes that slice of the output (finish_chunk).
+template <int NB>
+constexpr int kSlotVals = 2 + 4 * NB;  // state values per lane and head tile: m, l, NB x 4 outputs
+
+template <int NT, int NB>
+__device__ __forceinline__ void publish_wave(const TileReducer<NT, NB>& red, float* slots, int wave, int lane) {
+  constexpr int SV = kSlotVals<NB>;
+  float* v0 = slots + (size_t)wave * (NT * SV * 64) + lane;
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    float* v = v0 + nt * SV * 64;
+    v[0] = red.m[nt];
+    v[64] = sum_rows(red.l[nt]);
+#pragma unroll
+    for (int nn = 0; nn < NB; ++nn)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[(2 + nn * 4 + i) * 64] = red.o[nt][nn][i];
+  }
+}
+
+// direct: the chunk is the whole sequence and the normalised output is
+// written (rows row0_tile + h); otherwise the chunk state (state rows srow0 +
+// h), with device-scope stores where p.mode is kFused.  nb0: first 16-dim
+// block of this workgroup's V slice.  With fewer blocks than waves (V slices)
+// waves 0 .. NB - 1 merge one block each.
+template <int NT, int NB, int W>
+__device__ __forceinline__ void finish_chunk(const Params& p, const float* slots, bool direct, int64_t row0_tile,
+                                             int64_t srow0, int nb0, int wave, int lane) {
+  static_assert(NB % W == 0 || W % NB == 0, "blocks must divide among the waves");
+  constexpr int NBW = NB >= W ? NB / W : 1;
+  constexpr int SV = kSlotVals<NB>;
+  const int col = lane & 15, quad = lane >> 4;
+  const bool merges = NB >= W || wave < NB;
+  auto slot = [&](int w) { return slots + (size_t)w * (NT * SV * 64); };
+  const __amdgpu_buffer_rsrc_t ors = make_rsrc(p.o_part + srow0 * D, (uint32_t)p.hpt * D * 4);
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    float mk[W], wk[W];
+    float M = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+      mk[k] = slot(k)[nt * SV * 64 + lane];
+      M = fmaxf(M, mk[k]);
+    }
+    float Lw = 0.f;
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+      wk[k] = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mk[k] - M);  // all empty: stays empty
+      Lw = fmaf(wk[k], slot(k)[(nt * SV + 1) * 64 + lane], Lw);
+    }
+    // lane (col, quad) owns dims 16(nb0 + nn) + 4quad + [0, 4) of head
+    // 16nt + col, nn = wave * NBW + bb
+    f32x4 o[NBW];
+#pragma unroll
+    for (int bb = 0; bb < NBW; ++bb) {
+      const int nn = merges ? wave * NBW + bb : 0;
+      o[bb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k = 0; k < W; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          o[bb][i] = fmaf(wk[k], slot(k)[(nt * SV + 2 + nn * 4 + i) * 64 + lane], o[bb][i]);
+    }
+    const int h = nt * 16 + col;
+    if (h >= p.hpt || !merges) continue;
+    const int64_t row = row0_tile + h;
+    const float mval = Lw > 0.f ? M * kLn2 : -INFINITY;
+    if (direct) {
+      const float inv = Lw > 0.f ? 1.0f / Lw : 0.f;
+#pragma unroll
+      for (int bb = 0; bb < NBW; ++bb) {
+        const int nn = nb0 + wave * NBW + bb;
+        *reinterpret_cast<uint2*>(p.out + row * D + 16 * nn + 4 * quad) =
+            make_uint2(pack_bf16x2(o[bb][0] * inv, o[bb][1] * inv), pack_bf16x2(o[bb][2] * inv, o[bb][3] * inv));
+      }
+      if (p.lse && wave == 0 && quad == 0 && nb0 == 0) p.lse[row] = Lw > 0.f ? mval + logf(Lw) : -INFINITY;
+    } else if (p.mode == kPartials) {
+#pragma unroll
+      for (int bb = 0; bb < NBW; ++bb) {
+        const int nn = nb0 + wave * NBW + bb;
+        const u32x4 bits = {__float_as_uint(o[bb][0]), __float_as_uint(o[bb][1]), __float_as_uint(o[bb][2]),
+                            __float_as_uint(o[bb][3])};
+        __builtin_amdgcn_raw_buffer_store_b128(bits, ors, (uint32_t)(h * D + 16 * nn + 4 * quad) * 4u, 0, 0);
+      }
+      if (wave == 0 && quad == 0 && nb0 == 0) {
+        p.m_part[srow0 + h] = mval;
+        p.l_part[srow0 + h] = Lw;
+      }
+    } else {
+      // kFused: device-scope stores write the chunk state through L2, so
+      // it is visible to every XCD once the stores have completed
+#pragma unroll
+      for (int bb = 0; bb < NBW; ++bb) {
+        const int nn = nb0 + wave * NBW + bb;
+        const u32x4 bits = {__float_as_uint(o[bb][0]), __float_as_uint(o[bb][1]), __float_as_uint(o[bb][2]),
+                            __float_as_uint(o[bb][3])};
+        __builtin_amdgcn_raw_buffer_store_b128(bits, ors, (uint32_t)(h * D + 16 * nn + 4 * quad) * 4u, 0,
+                                               kDeviceScope);
+      }
+      if (wave == 0 && quad == 0 && nb0 == 0) {
+        __hip_atomic_store(p.m_part + srow0 + h, mval, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(p.l_part + srow0 + h, Lw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+  }
 }
 
 // Waves per SIMD each variant must fit: three for the 16-column direct-fetch
@@ -625,32 +900,11 @@ split_partial_kernel(Params p) {
     }
   };
 
-  // ---- Q^T as the MFMA B operand.  The reduction index of the product may
-  //      map to head dims in any order as long as K and Q agree: k-step j,
-  //      lane group `quad` covers dims [32j + 8*quad, +8).  Lane holds those
-  //      dims of head column `col` (zeros for padding).
-  bf16x8 qreg[NT][4];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int h = nt * 16 + col;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      u32x4 x = {0u, 0u, 0u, 0u};
-      if (h < p.hpt)
-        x = *reinterpret_cast<const u32x4*>(p.q + ((int64_t)b * p.H_Q + head0 + h) * D + 32 * j + 8 * quad);
-      qreg[nt][j] = as_bf16x8(x);
-    }
-  }
-
-  float m_run[NT], l_run[NT];
-  f32x4 acc_o[NT][NB];  // output blocks nb0 .. nb0 + NB - 1
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    m_run[nt] = -INFINITY;
-    l_run[nt] = 0.f;
-#pragma unroll
-    for (int nn = 0; nn < NB; ++nn) acc_o[nt][nn] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+  TileReducer<NT, NB> red;  // output blocks nb0 .. nb0 + NB - 1
+  red.scale_log2 = p.scale_log2;
+  red.quad = quad;
+  red.load_q(p.q + ((int64_t)b * p.H_Q + head0) * D, p.hpt, col);
+  red.reset();
 
   constexpr bool KS = FETCH == kFetchStaged;
   unsigned char* vstage = smem + wave * stage_bytes(FETCH);
@@ -694,121 +948,6 @@ split_partial_kernel(Params p) {
     for (int jj = 0; jj < 8; ++jj) vreg[jj] = __builtin_amdgcn_raw_buffer_load_b128(vt, voff[jj], 0, kv_aux);
   };
 
-  // S^T[16 keys x 16 heads] per (mt, nt) from the tile's 8 K operands.
-  auto scores = [&](const bf16x8 (&kop)[2][4], f32x4 (&sc)[NT][2]) {
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[mt][j], qreg[nt][j], acc, 0, 0, 0);
-        sc[nt][mt] = acc;
-      }
-  };
-
-  // Online softmax per head column, in log2 units of the scaled score: the
-  // max is taken on raw scores (the scale is positive) and each exponent is
-  // one fma, raw * scale*log2(e) - running max.  `last`: only the final tile
-  // can be shorter than 32 keys and needs its scores masked.
-  auto softmax = [&](f32x4 (&sc)[NT][2], int nvalid, auto last, bf16x8 (&pb)[NT]) {
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      float x[8];
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          float r = sc[nt][mt][i];
-          if constexpr (decltype(last)::value) r = (mt * 16 + quad * 4 + i) < nvalid ? r : -INFINITY;
-          x[mt * 4 + i] = r;
-        }
-      const float rmax = max_rows(fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])),
-                                        fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7]))));
-      const float m_new = fmaxf(m_run[nt], rmax * p.scale_log2);
-      const float alpha = __builtin_amdgcn_exp2f(m_run[nt] - m_new);
-      float psum = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        x[e] = __builtin_amdgcn_exp2f(fmaf(x[e], p.scale_log2, -m_new));
-        psum += x[e];
-      }
-      l_run[nt] = l_run[nt] * alpha + psum;
-      m_run[nt] = m_new;
-      // alpha == 1 exactly when the column max did not move: skip the
-      // multiply by one (a wave-uniform branch)
-      if (__any(alpha != 1.0f)) {
-#pragma unroll
-        for (int nn = 0; nn < NB; ++nn) acc_o[nt][nn] *= alpha;
-      }
-      u32x4 pk;
-      pk.x = pack_bf16x2(x[0], x[1]);
-      pk.y = pack_bf16x2(x[2], x[3]);
-      pk.z = pack_bf16x2(x[4], x[5]);
-      pk.w = pack_bf16x2(x[6], x[7]);
-      pb[nt] = as_bf16x8(pk);
-    }
-  };
-
-  // O^T[16 dims x 16 heads] += V^T[16 dims x 32 keys] . P^T[32 keys x 16 heads]
-  // The k index 8*quad + 4*mt + i of the product stands for key
-  // 16*mt + 4*quad + i, matching the score layout.  The V^T operand comes
-  // from transposing LDS reads (ds_read_b64_tr_b16): within each 16-lane
-  // group, output lane j receives element j%4 of the 8-byte chunks that
-  // lanes 4k + j/4 point at, k = 0..3.  Lane (quad, 4k + m) therefore points
-  // at dims [16nn + 4m, +4) of key 16mt + 4quad + k -- vaddr(mt, nn) gives
-  // that address for the stage layout in use -- and lane (quad, col)
-  // receives V[16mt + 4quad + k][16nn + col] for k = 0..3.  All 16 reads are
-  // issued before the first product so their LDS latency is paid once per
-  // tile rather than once per 16 output dims.
-  // With direct-to-LDS loads in flight (`opaque`; vaddr then gives LDS byte
-  // offsets), the reads are written as inline assembly followed by an
-  // explicit wait: the compiler cannot tell that they touch the other stage
-  // and would otherwise drain every outstanding load before them.
-  auto pv = [&](const bf16x8 (&pb)[NT], auto vaddr, auto opaque) {
-    s16x4 vlo[NB], vhi[NB];
-    if constexpr (decltype(opaque)::value) {
-#pragma unroll
-      for (int nn = 0; nn < NB; ++nn) {
-        asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(vlo[nn]) : "v"((uint32_t)vaddr(0, nn)) : "memory");
-        asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(vhi[nn]) : "v"((uint32_t)vaddr(1, nn)) : "memory");
-      }
-      // The wait names every result as an operand it updates, so nothing
-      // that reads them can be scheduled before it.
-      if constexpr (NB == 8)
-        asm volatile("s_waitcnt lgkmcnt(0)"
-                     : "+v"(vlo[0]), "+v"(vlo[1]), "+v"(vlo[2]), "+v"(vlo[3]), "+v"(vlo[4]), "+v"(vlo[5]),
-                       "+v"(vlo[6]), "+v"(vlo[7]), "+v"(vhi[0]), "+v"(vhi[1]), "+v"(vhi[2]), "+v"(vhi[3]),
-                       "+v"(vhi[4]), "+v"(vhi[5]), "+v"(vhi[6]), "+v"(vhi[7])
-                     :
-                     : "memory");
-      else if constexpr (NB == 4)
-        asm volatile("s_waitcnt lgkmcnt(0)"
-                     : "+v"(vlo[0]), "+v"(vlo[1]), "+v"(vlo[2]), "+v"(vlo[3]), "+v"(vhi[0]), "+v"(vhi[1]),
-                       "+v"(vhi[2]), "+v"(vhi[3])
-                     :
-                     : "memory");
-      else
-        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(vlo[0]), "+v"(vlo[1]), "+v"(vhi[0]), "+v"(vhi[1]) : : "memory");
-    } else {
-#pragma unroll
-      for (int nn = 0; nn < NB; ++nn) {
-        vlo[nn] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)vaddr(0, nn));
-        vhi[nn] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)vaddr(1, nn));
-      }
-    }
-    __builtin_amdgcn_sched_group_barrier(0x100, 2 * NB, 0);   // the DS reads first
-    __builtin_amdgcn_sched_group_barrier(0x008, NB * NT, 0);  // then the MFMAs
-#pragma unroll
-    for (int nn = 0; nn < NB; ++nn) {
-      const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(vlo[nn], vhi[nn], 0, 1, 2, 3, 4, 5, 6, 7));
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-        acc_o[nt][nn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pb[nt], acc_o[nt][nn], 0, 0, 0);
-    }
-  };
-
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
   if constexpr (FETCH != kFetchLds) {
@@ -844,7 +983,7 @@ split_partial_kernel(Params p) {
           for (int j = 0; j < 4; ++j) kop[mt][j] = as_bf16x8(kreg[mt][j]);
       }
       f32x4 sc[NT][2];
-      scores(kop, sc);
+      red.scores(kop, sc);
 
       // stage V rows in LDS (row-major, padded pitch)
 #pragma unroll
@@ -854,10 +993,10 @@ split_partial_kernel(Params p) {
       if constexpr (decltype(prefetch)::value) load_tile(kreg, vreg, t + 1);
 
       bf16x8 pb[NT];
-      softmax(sc, nvalid, last, pb);
+      red.softmax(sc, nvalid, last, pb);
       __builtin_amdgcn_wave_barrier();
       const unsigned char* vrow = vstage + (quad * 4 + (col >> 2)) * kVPitch + 8 * (col & 3);
-      pv(pb, [&](int mt, int nn) { return vrow + mt * 16 * kVPitch + 32 * nn; }, no);
+      red.pv(pb, [&](int mt, int nn) { return vrow + mt * 16 * kVPitch + 32 * nn; }, no);
       __builtin_amdgcn_wave_barrier();
     };
 
@@ -936,10 +1075,10 @@ split_partial_kernel(Params p) {
           kop[mt][j] = as_bf16x8(*reinterpret_cast<const __attribute__((address_space(3))) u32x4*>(
               (uintptr_t)(kro[mt][j] + so)));
       f32x4 sc[NT][2];
-      scores(kop, sc);
+      red.scores(kop, sc);
       bf16x8 pb[NT];
-      softmax(sc, key_hi - (key_lo + t * kstep), last, pb);
-      pv(pb, [&](int mt, int nn) { return vro[mt][nn] + so; }, yes);
+      red.softmax(sc, key_hi - (key_lo + t * kstep), last, pb);
+      red.pv(pb, [&](int mt, int nn) { return vro[mt][nn] + so; }, yes);
     };
     // The compiler cannot see that the LDS reads depend on the direct-to-LDS
     // loads, so the waits are explicit: 16 loads per tile, completing in
@@ -972,115 +1111,15 @@ split_partial_kernel(Params p) {
     }
   }
 
-  // ---- merge the W wave states in one step.  Every wave publishes its
-  //      state (per head column: running max, row-summed l, 8 x 4 output
-  //      values; all waves share one lane layout) to LDS value-major
-  //      ([value][lane], conflict-free).  After one barrier, wave w merges
-  //      the W states for its 8/W blocks of 16 output dims -- maximum,
-  //      weights, then sums taken in wave order, so the result is the same
-  //      on every run -- and writes that slice of the output.
-  // With fewer blocks than waves (V slices) waves 0 .. NB - 1 merge one
-  // block each and the others only take part in the exchange.
-  static_assert(NB % W == 0 || W % NB == 0, "blocks must divide among the waves");
-  constexpr int NBW = NB >= W ? NB / W : 1;
-  constexpr int SV = 2 + 4 * NB;  // state values per lane and head tile: m, l, NB x 4 outputs
-  const bool merges = NB >= W || wave < NB;
-  float lsum[NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) lsum[nt] = sum_rows(l_run[nt]);
-  auto slot = [&](int w) { return reinterpret_cast<float*>(smem) + (size_t)w * (NT * SV * 64); };
-  __syncthreads();  // every wave is done with its stages
-  {
-    float* v0 = slot(wave) + lane;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      float* v = v0 + nt * SV * 64;
-      v[0] = m_run[nt];
-      v[64] = lsum[nt];
-#pragma unroll
-      for (int nn = 0; nn < NB; ++nn)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[(2 + nn * 4 + i) * 64] = acc_o[nt][nn][i];
-    }
-  }
-  __syncthreads();
-
   const int64_t rows = (int64_t)p.B * p.H_Q;
   const int64_t row0_tile = (int64_t)b * p.H_Q + head0;
   const bool direct = SCH ? prow < 0 : p.mode == kDirect;
   // first chunk-state row of this workgroup's heads
   const int64_t srow0 = direct ? 0 : (SCH ? (int64_t)prow * p.H_Q + head0 : (int64_t)split * rows + row0_tile);
-  const __amdgpu_buffer_rsrc_t ors = make_rsrc(p.o_part + srow0 * D, (uint32_t)p.hpt * D * 4);
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    float mk[W], wk[W];
-    float M = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < W; ++k) {
-      mk[k] = slot(k)[nt * SV * 64 + lane];
-      M = fmaxf(M, mk[k]);
-    }
-    float Lw = 0.f;
-#pragma unroll
-    for (int k = 0; k < W; ++k) {
-      wk[k] = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mk[k] - M);  // all empty: stays empty
-      Lw = fmaf(wk[k], slot(k)[(nt * SV + 1) * 64 + lane], Lw);
-    }
-    // lane (col, quad) owns dims 16(nb0 + nn) + 4quad + [0, 4) of head
-    // 16nt + col, nn = wave * NBW + bb
-    f32x4 o[NBW];
-#pragma unroll
-    for (int bb = 0; bb < NBW; ++bb) {
-      const int nn = merges ? wave * NBW + bb : 0;
-      o[bb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int k = 0; k < W; ++k)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          o[bb][i] = fmaf(wk[k], slot(k)[(nt * SV + 2 + nn * 4 + i) * 64 + lane], o[bb][i]);
-    }
-    const int h = nt * 16 + col;
-    if (h >= p.hpt || !merges) continue;
-    const int64_t row = row0_tile + h;
-    const float mval = Lw > 0.f ? M * kLn2 : -INFINITY;
-    if (direct) {
-      const float inv = Lw > 0.f ? 1.0f / Lw : 0.f;
-#pragma unroll
-      for (int bb = 0; bb < NBW; ++bb) {
-        const int nn = nb0 + wave * NBW + bb;
-        *reinterpret_cast<uint2*>(p.out + row * D + 16 * nn + 4 * quad) =
-            make_uint2(pack_bf16x2(o[bb][0] * inv, o[bb][1] * inv), pack_bf16x2(o[bb][2] * inv, o[bb][3] * inv));
-      }
-      if (p.lse && wave == 0 && quad == 0 && nb0 == 0) p.lse[row] = Lw > 0.f ? mval + logf(Lw) : -INFINITY;
-    } else if (p.mode == kPartials) {
-#pragma unroll
-      for (int bb = 0; bb < NBW; ++bb) {
-        const int nn = nb0 + wave * NBW + bb;
-        const u32x4 bits = {__float_as_uint(o[bb][0]), __float_as_uint(o[bb][1]), __float_as_uint(o[bb][2]),
-                            __float_as_uint(o[bb][3])};
-        __builtin_amdgcn_raw_buffer_store_b128(bits, ors, (uint32_t)(h * D + 16 * nn + 4 * quad) * 4u, 0, 0);
-      }
-      if (wave == 0 && quad == 0 && nb0 == 0) {
-        p.m_part[srow0 + h] = mval;
-        p.l_part[srow0 + h] = Lw;
-      }
-    } else {
-      // kFused: device-scope stores write the chunk state through L2, so
-      // it is visible to every XCD once the stores have completed
-#pragma unroll
-      for (int bb = 0; bb < NBW; ++bb) {
-        const int nn = nb0 + wave * NBW + bb;
-        const u32x4 bits = {__float_as_uint(o[bb][0]), __float_as_uint(o[bb][1]), __float_as_uint(o[bb][2]),
-                            __float_as_uint(o[bb][3])};
-        __builtin_amdgcn_raw_buffer_store_b128(bits, ors, (uint32_t)(h * D + 16 * nn + 4 * quad) * 4u, 0,
-                                               kDeviceScope);
-      }
-      if (wave == 0 && quad == 0 && nb0 == 0) {
-        __hip_atomic_store(p.m_part + srow0 + h, mval, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(p.l_part + srow0 + h, Lw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
-  }
+  __syncthreads();  // every wave is done with its stages
+  publish_wave(red, reinterpret_cast<float*>(smem), wave, lane);
+  __syncthreads();
+  finish_chunk<NT, NB, W>(p, reinterpret_cast<const float*>(smem), direct, row0_tile, srow0, nb0, wave, lane);
 
   // Two-wave kernels never merge in the launch (their plans use the second
   // launch; the merge's batches are sized for four waves).
@@ -1129,6 +1168,395 @@ split_partial_kernel(Params p) {
     __syncthreads();
     if (!s_last) return;
     merge_tile<NT, W>(p, reinterpret_cast<float*>(smem), srow_m, cstride, s_m, row0_tile, nrows, tid);
+  }
+}
+
+// Inclusive prefix sum and maximum over the 64 lanes of a wave (DPP row
+// shifts, then row broadcasts), for non-negative values.
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
+__device__ __forceinline__ int wave_top(int x) {
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
+  return __builtin_amdgcn_readlane(x, 63);
+}
+
+// A workgroup barrier that orders LDS only: tile loads in flight stay in
+// flight (__syncthreads would wait for them).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// LDS of one workgroup of the dealt launch: the per-wave K and V stages, and
+// apart from them (the next tile's loads are in flight while a chunk is
+// finished) the wave-state slots.
+constexpr int dealt_smem_bytes(int W, int NT) {
+  return W * stage_bytes(kFetchStaged) + W * merge_slot_bytes(NT);
+}
+
+// The dealt launch, for batches whose lengths the device holds: p.groups
+// workgroups per head tile share the batch's 32-key tiles evenly, whatever
+// the lengths.  The tiles of all sequences are laid end to end (an empty
+// sequence counts one), and workgroup j of a head tile takes the tiles [j
+// per, (j + 1) per): the end of one sequence, whole sequences, and the start
+// of another.  per is the least length that covers the batch and gives no
+// sequence more than 64 pieces (and a few tiles at the least, see below).
+// Whole sequences are written at once; of the two it shares with its
+// neighbours, each workgroup writes the chunk states, and the last workgroup
+// to arrive at a sequence's head tile merges them (the hand-off of
+// split_partial_kernel).
+//
+// Every wave finds the deal for itself from the lengths (one load per 64
+// sequences, scanned across the lanes; 0.7-1.0 us).  K and V take the
+// register-staged path with one tile in flight per wave and two waves (8 MiB
+// in flight over the chip, see group_waves; four where a head tile is two
+// columns wide and the reduction weighs as much as the loads).  The next tile
+// is fetched before the current one is reduced, across sequences too, so that
+// a workgroup's stream of loads does not drain where it passes from one
+// sequence to the next, and Q of the next sequence is fetched while this one
+// streams.  The ticket of a workgroup's first shared chunk is taken two tiles
+// into the next sequence, when its stores are complete anyway, so that one
+// merge, not two, is left at the end.
+//
+// Bound by HBM: 32 sequences of 1024 to 16384 keys over 8 KV heads (1.06
+// GB) 234 -> 164 us against one split for all (6.4 TB/s; workgroups end
+// within 8% of each other, which is what is lost against equal lengths: 32 of
+// 8192 keys take 150.5 us, 7.1 TB/s), 64 sequences of 140 to 22365 keys over
+// 4 KV heads in 64-key pages (0.5 GB) 258 -> 88 us.  Four waves measured 4%
+// slower on both; two workgroups a CU 3-6%.  The fixed part is about 8 us, of
+// it 2-4 for the merge, so short batches stay with one split count
+// (prefers_dealt), and no workgroup takes fewer tiles than about the square
+// root of the longest sequence's: fewer, longer pieces, whose merge is
+// cheaper, cost no more than the stream saves.
+template <int NT, int W, bool PG, bool NTL>
+__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(1, 8))) dealt_kernel(Params p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr int kv_aux = NTL ? 2 : 0;
+  constexpr int NB = 8;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 15;
+  const int quad = lane >> 4;
+
+  // ---- this workgroup's head tile and its place among the head tile's
+  //      workgroups.  The head tiles that read one KV head share an XCD
+  //      (workgroup i starts on XCD i % 8), except in a last partial block.
+  int at = blockIdx.x;
+  {
+    const int readers = p.g / p.hpt;
+    const int blk = 8 * readers;
+    const int n = gridDim.x;
+    if (readers > 1 && at < n - n % blk) {
+      const int r = at % blk;
+      at += (r % 8) * readers + r / 8 - r;
+    }
+  }
+  const int j = div_by(at, p.div_tps);
+  const int ht = at - j * p.tiles_per_seq;
+  const int head0 = ht * p.hpt;
+  const int kvh = div_by(head0, p.div_g);
+
+  // ---- the deal.  Lane i of the window holds sequence win + i: its length
+  //      and (packed) first row.
+  int win_len = 0, win_row = 0, win = 0;
+  auto window = [&](int b0) {
+    const int b = b0 + lane;
+    int len = 0, row = 0;
+    if (b < p.B) {
+      if constexpr (PG) {
+        len = p.seq_lens[b];
+      } else {
+        row = p.cu[b];
+        len = p.cu[b + 1] - row;
+      }
+    }
+    win = b0;
+    win_row = row;
+    win_len = len < 0 ? 0 : (len > p.L_K ? p.L_K : len);
+  };
+  auto lane_tiles = [&]() {  // tiles dealt for the lane's sequence
+    const int t = (win_len + kKeysPerTile - 1) / kKeysPerTile;
+    return win + lane < p.B ? max(t, 1) : 0;
+  };
+  int sum = 0, top = 0;
+  for (int b0 = 0; b0 < p.B; b0 += 64) {
+    window(b0);
+    const int t = lane_tiles();
+    sum += t;
+    top = max(top, t);
+  }
+  const int total = __builtin_amdgcn_readlane(wave_scan(sum), 63);
+  top = wave_top(top);
+  int per = (total + p.groups - 1) / p.groups;
+  per = max(max(per, (top + DA_MAX_SPLITS - 2) / (DA_MAX_SPLITS - 1)),
+            max(4, (int)((NT == 1 ? 0.7f : 1.1f) * __builtin_sqrtf((float)top))));
+  const int lo = j * per;
+  const int hi = min(lo + per, total);
+  if (lo >= total) return;  // the whole workgroup: fewer pieces than workgroups
+  int b = 0, start = 0;     // the sequence tile `lo` is in, and that sequence's first tile
+  for (int b0 = 0, before = 0; b0 < p.B; b0 += 64) {
+    if (p.B > 64) window(b0);
+    const int t = lane_tiles();
+    const int incl = wave_scan(t);
+    const uint64_t past = __ballot(before + incl > lo);
+    if (past) {
+      const int i = __ffsll((unsigned long long)past) - 1;
+      b = b0 + i;
+      start = before + __builtin_amdgcn_readlane(incl - t, i);
+      break;
+    }
+    before += __builtin_amdgcn_readlane(incl, 63);
+  }
+
+  // ---- segments: the part of one sequence this workgroup takes
+  struct Segment {
+    int b, start;     // sequence, its first tile in the deal
+    int len, row0;    // its keys, its first row (packed)
+    int tiles;        // tiles it counts for
+    int t0, nt;       // tiles taken here that hold keys: [t0, t0 + nt)
+    int end;          // the deal's tile after this segment
+    int t, step, n;   // this wave's first tile, its stride, its tile count
+    int pg_win, pg_ids;  // paged: the 64 page ids from page pg_win on, one per lane
+  };
+  // Two waves over key rows of at most 1 KiB take a segment's tiles
+  // alternately, otherwise each takes a contiguous part (as in
+  // split_partial_kernel).
+  const bool alternate = W == 2 && p.H_KV <= 4;
+  auto pages = [&](Segment& s, int first_page) {
+    const int last = s.n > 0 ? div_by(s.len - 1, p.div_page) : -1;
+    const int jj = first_page + lane;
+    s.pg_win = first_page;
+    s.pg_ids = jj <= last ? p.block_table[(int64_t)s.b * p.max_pages + jj] : 0;
+  };
+  auto segment = [&](int sb, int sstart, int from) {
+    Segment s;
+    if (sb - win >= 64) window(sb);
+    s.b = sb;
+    s.start = sstart;
+    s.len = __builtin_amdgcn_readlane(win_len, sb - win);
+    s.row0 = __builtin_amdgcn_readlane(win_row, sb - win);
+    const int full = (s.len + kKeysPerTile - 1) / kKeysPerTile;
+    s.tiles = max(full, 1);
+    s.t0 = from - sstart;
+    s.end = min(hi, sstart + s.tiles);
+    s.nt = min(s.end - sstart, full) - s.t0;  // 0 for an empty sequence
+    if (alternate) {
+      s.t = s.t0 + wave;
+      s.step = W;
+      s.n = (s.nt - wave + W - 1) / W;
+    } else {
+      s.t = s.t0 + s.nt * wave / W;
+      s.step = 1;
+      s.n = s.t0 + s.nt * (wave + 1) / W - s.t;
+    }
+    s.pg_win = 0;
+    s.pg_ids = 0;
+    if constexpr (PG) pages(s, div_by(s.t * kKeysPerTile, p.div_page));
+    return s;
+  };
+
+  // ---- K/V tiles (as split_partial_kernel's register-staged path)
+  const uint32_t rs = (uint32_t)p.H_KV * (D * 2);
+  uint32_t voff[8];
+#pragma unroll
+  for (int jj = 0; jj < 8; ++jj) voff[jj] = (uint32_t)(4 * jj + quad) * rs + 16u * col;
+  u32x4 kreg[8], vreg[8];
+  // First element and byte count of the segment's tile i of this wave.
+  auto place = [&](Segment& s, int i, int64_t& elems, uint32_t& bytes) {
+    const int first = (s.t + i * s.step) * kKeysPerTile;
+    bytes = (uint32_t)min(s.len - first, kKeysPerTile) * rs;
+    int64_t row;
+    if constexpr (PG) {
+      const int pg = div_by(first, p.div_page);
+      if (pg - s.pg_win >= 64) pages(s, pg);
+      const int page = __builtin_amdgcn_readlane(s.pg_ids, pg - s.pg_win);
+      const bool in = page >= 0 && page < p.num_pages;  // a page id outside the cache reads as zeros
+      if (!in) bytes = 0u;
+      row = (int64_t)(in ? page : 0) * p.page_size + (first - pg * p.page_size);
+    } else {
+      row = (int64_t)s.row0 + first;
+    }
+    elems = (row * p.H_KV + kvh) * D;
+  };
+  auto load_tile = [&](int64_t elems, uint32_t bytes) {
+    // (uniform already; said so for the compiler, which would loop over lanes otherwise)
+    elems = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(elems >> 32)) << 32) |
+                      (uint32_t)__builtin_amdgcn_readfirstlane((int)elems));
+    bytes = (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes);
+    const __amdgpu_buffer_rsrc_t kt = make_rsrc(p.k + elems, bytes);
+    const __amdgpu_buffer_rsrc_t vt = make_rsrc(p.v + elems, bytes);
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj) kreg[jj] = __builtin_amdgcn_raw_buffer_load_b128(kt, voff[jj], 0, kv_aux);
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj) vreg[jj] = __builtin_amdgcn_raw_buffer_load_b128(vt, voff[jj], 0, kv_aux);
+  };
+  // Q of a segment (rows past the head tile read as zeros)
+  u32x4 qnext[NT][4];
+  auto load_q = [&](const Segment& s) {
+    const __amdgpu_buffer_rsrc_t qr =
+        make_rsrc(p.q + ((int64_t)s.b * p.H_Q + head0) * D, (uint32_t)p.hpt * (D * 2));
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj)
+        qnext[nt][jj] = __builtin_amdgcn_raw_buffer_load_b128(
+            qr, (uint32_t)(nt * 16 + col) * (D * 2) + 64u * jj + 16u * quad, 0, 0);
+  };
+
+  TileReducer<NT, NB> red;
+  red.scale_log2 = p.scale_log2;
+  red.quad = quad;
+  unsigned char* vstage = smem + wave * stage_bytes(kFetchStaged);
+  unsigned char* kstage = vstage + kKeysPerTile * kVPitch;
+  float* slots = reinterpret_cast<float*>(smem + W * stage_bytes(kFetchStaged));
+  constexpr std::false_type no{};
+
+  // The chunks this workgroup shares: of the sequence it begins in the
+  // middle of (state slot 2 j) and of the one it leaves unfinished (slot 2 j
+  // + 1).  first: the sequence's first workgroup; pieces: how many share it.
+  struct Part {
+    int b = 0, first = 0, pieces = 0;
+  } part_head, part_tail;
+  __shared__ int s_last[2];
+  if (tid < 2) s_last[tid] = 0;  // read past barriers only
+  // One ticket per wave and shared chunk, taken once the wave's stores have
+  // completed; whoever takes a sequence's last one has its workgroup merge.
+  auto arrive = [&](const Part& part, int which) {
+    if (lane == 0) {
+      uint32_t* counter = p.arrivals + ((size_t)part.b * p.tiles_per_seq + ht) * da::kArrivalStride;
+      if (__hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
+          (uint32_t)(part.pieces * W)) {
+        __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_last[which] = 1;
+      }
+    }
+  };
+
+  Segment cur = segment(b, start, lo);
+  int64_t elems = 0;
+  uint32_t bytes = 0;
+  if (cur.n > 0) place(cur, 0, elems, bytes);
+  load_tile(elems, bytes);
+  bool loaded = cur.n > 0;  // kreg and vreg hold (or await) this segment's first tile
+  load_q(cur);
+  int owed = 0;        // the head chunk's ticket is not taken yet: the tiles until it is
+  for (;;) {
+    const bool more = cur.end < hi;
+    Segment nxt = cur;
+    if (more) nxt = segment(cur.b + 1, cur.end, cur.end);
+    if (!loaded && cur.n > 0) {
+      place(cur, 0, elems, bytes);
+      load_tile(elems, bytes);
+    }
+    loaded = false;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) {
+        // wait for Q here (the first tile is needed next anyway), not in every iteration of the loop below
+        asm volatile("" : "+v"(qnext[nt][jj]));
+        red.q[nt][jj] = as_bf16x8(qnext[nt][jj]);
+      }
+    load_q(nxt);
+    red.reset();
+    for (int i = 0; i < cur.n; ++i) {
+      bf16x8 kop[2][4];
+#pragma unroll
+      for (int jj = 0; jj < 8; ++jj)
+        *reinterpret_cast<u32x4*>(kstage + (4 * jj + quad) * kKPitch + 16 * col) = kreg[jj];
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj)
+          kop[mt][jj] =
+              as_bf16x8(*reinterpret_cast<const u32x4*>(kstage + (16 * mt + col) * kKPitch + 16 * (4 * jj + quad)));
+      f32x4 sc[NT][2];
+      red.scores(kop, sc);
+#pragma unroll
+      for (int jj = 0; jj < 8; ++jj)
+        *reinterpret_cast<u32x4*>(vstage + (4 * jj + quad) * kVPitch + 16 * col) = vreg[jj];
+      if (owed && --owed == 0) {  // the head chunk's stores are a tile old and alone outstanding: no stall
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        arrive(part_head, 0);
+      }
+      // the next tile: this segment's, or the next one's first (or nothing: reads of no bytes)
+      bytes = 0;
+      if (i + 1 < cur.n) {
+        place(cur, i + 1, elems, bytes);
+      } else if (more && nxt.n > 0) {
+        place(nxt, 0, elems, bytes);
+        loaded = true;
+      }
+      load_tile(elems, bytes);
+      const int nvalid = cur.len - (cur.t + i * cur.step) * kKeysPerTile;  // >= 1
+      if (nvalid < kKeysPerTile) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sc[nt][mt][e] = mt * 16 + quad * 4 + e < nvalid ? sc[nt][mt][e] : -INFINITY;
+      }
+      bf16x8 pb[NT];
+      red.softmax(sc, kKeysPerTile, no, pb);
+      __builtin_amdgcn_wave_barrier();
+      const unsigned char* vrow = vstage + (quad * 4 + (col >> 2)) * kVPitch + 8 * (col & 3);
+      red.pv(pb, [&](int mt, int nn) { return vrow + mt * 16 * kVPitch + 32 * nn; }, no);
+      __builtin_amdgcn_wave_barrier();
+    }
+
+    // finish the segment: whole sequences are written, shared ones leave their state
+    const bool head = cur.start < lo, tail = cur.start + cur.tiles > hi;
+    if (head || tail) {
+      Part part;
+      part.b = cur.b;
+      part.first = cur.start / per;
+      part.pieces = (cur.start + cur.tiles - 1) / per - part.first + 1;
+      if (head)
+        part_head = part;
+      else
+        part_tail = part;
+    }
+    lds_barrier();  // the last segment's slots have been read
+    publish_wave(red, slots, wave, lane);
+    lds_barrier();
+    finish_chunk<NT, NB, W>(p, slots, !(head || tail), (int64_t)cur.b * p.H_Q + head0,
+                            (int64_t)(2 * j + (head ? 0 : 1)) * p.H_Q + head0, 0, wave, lane);
+    if (head) owed = 2;
+    if (!more) break;
+    cur = nxt;
+  }
+
+  // ---- the shared sequences' merges (hand-off as in split_partial_kernel)
+  if (part_head.pieces == 0 && part_tail.pieces == 0) return;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (owed) arrive(part_head, 0);
+  if (part_tail.pieces) arrive(part_tail, 1);
+  __syncthreads();
+#pragma unroll 1
+  for (int k = 0; k < 2; ++k) {
+    if (!s_last[k]) continue;  // uniform
+    const Part part = k == 0 ? part_head : part_tail;
+    merge_tile<NT, W, true>(p, reinterpret_cast<float*>(smem), (int64_t)2 * part.first * p.H_Q + head0,
+                            (int64_t)2 * p.H_Q, part.pieces, (int64_t)part.b * p.H_Q + head0,
+                            (int64_t)2 * p.groups * p.H_Q, tid, (uint32_t)p.H_Q);
+    __syncthreads();
   }
 }
 
@@ -1438,6 +1866,28 @@ int run_decode(Params p, int B, int H_Q, int H_KV, int L_K_max, int d, float sof
                         static_cast<hipStream_t>(stream));
 }
 
+// The dealt launch of `groups` workgroups per head tile (dealt_kernel).
+// `p` carries the K/V layout.
+int launch_dealt(const Params& prm, const da::DealtPlan& dp, hipStream_t stream) {
+  const bool paged = prm.block_table != nullptr;
+  const int NT = dp.heads_per_tile <= 16 ? 1 : 2;
+  const int W = NT == 1 ? 2 : 4;
+  auto pick = [&](auto nt) -> const void* {
+    constexpr int N = decltype(nt)::value, V = N == 1 ? 2 : 4;
+    if (paged)
+      return dp.kv_nontemporal ? reinterpret_cast<const void*>(&dealt_kernel<N, V, true, true>)
+                               : reinterpret_cast<const void*>(&dealt_kernel<N, V, true, false>);
+    return dp.kv_nontemporal ? reinterpret_cast<const void*>(&dealt_kernel<N, V, false, true>)
+                             : reinterpret_cast<const void*>(&dealt_kernel<N, V, false, false>);
+  };
+  const void* fn = NT == 1 ? pick(std::integral_constant<int, 1>{}) : pick(std::integral_constant<int, 2>{});
+  const int smem = dealt_smem_bytes(W, NT);
+  void* args[] = {const_cast<Params*>(&prm)};
+  hipError_t e = hipLaunchKernel(fn, dim3(dp.groups * prm.tiles_per_seq), dim3(64 * W), args, smem, stream);
+  if (e != hipSuccess) return da::fail(DA_ERR_HIP, "dealt launch: %s", hipGetErrorString(e));
+  return DA_OK;
+}
+
 // Checks of the paged layout arguments (shape already checked).
 int check_paged(const void* q, const void* k_cache, const void* v_cache, const int32_t* block_table,
                 const int32_t* seq_lens, int B, int page_size, int max_pages, int num_pages, int L_K_max) {
@@ -1745,6 +2195,58 @@ int da_decode_attn_scheduled(const void* q, const void* k, const void* v, const 
   if (rc || !need || sched->combine) return rc;
   return launch_combine(p.o_part, p.m_part, p.l_part, static_cast<uint16_t*>(out), lse_out, sched->max_splits,
                         (int64_t)B * H_Q, static_cast<hipStream_t>(stream), seqs, H_Q);
+}
+
+int da_decode_attn_dealt(const void* q, const void* k, const void* v, const int32_t* cu_seqlens_k,
+                         const int32_t* block_table, const int32_t* seq_lens, int page_size, int max_pages,
+                         int num_pages, void* out, float* lse_out, int B, int H_Q, int H_KV, int L_K_max, int d,
+                         float softmax_scale, int64_t keys, void* workspace, size_t workspace_bytes,
+                         void* stream) {
+  da::clear_error();
+  int rc = block_table ? check_paged_inputs(q, k, v, block_table, seq_lens, B, H_Q, H_KV, page_size, max_pages,
+                                            num_pages, L_K_max, d)
+                       : check_inputs(q, k, v, cu_seqlens_k, B, H_Q, H_KV, L_K_max, d);
+  if (rc) return rc;
+  if (!block_table && !cu_seqlens_k)
+    return da::fail(DA_ERR_NULL, "cu_seqlens_k, or block_table and seq_lens, must be non-NULL");
+  if (!out) return da::fail(DA_ERR_NULL, "out must be non-NULL");
+  if (!aligned(out, 16)) return da::fail(DA_ERR_ALIGN, "out must be 16-byte aligned");
+  if (lse_out && !aligned(lse_out, 4)) return da::fail(DA_ERR_ALIGN, "lse_out must be 4-byte aligned");
+  if (!workspace) return da::fail(DA_ERR_WORKSPACE, "the dealt launch needs a workspace");
+  if (!aligned(workspace, 16)) return da::fail(DA_ERR_ALIGN, "workspace must be 16-byte aligned");
+  int cus = 0;
+  rc = ensure_gfx950(&cus);
+  if (rc) return rc;
+  da::DealtPlan dp;
+  if (!da::dealt_plan(B, H_Q, H_KV, L_K_max, keys, cus, &dp))
+    return da::fail(DA_ERR_ARG, "B=%d H_Q=%d H_KV=%d is not a shape the dealt launch takes", B, H_Q, H_KV);
+  const da::WorkspaceLayout wl = da::workspace_layout(2 * dp.groups, H_Q, d, 1);
+  if (workspace_bytes < wl.total)
+    return da::fail(DA_ERR_WORKSPACE, "the dealt launch needs %zu workspace bytes, got %zu", wl.total, workspace_bytes);
+  Params p{};
+  if (block_table) {
+    set_paged(p, q, k, v, block_table, seq_lens, page_size, max_pages, num_pages);
+  } else {
+    p.q = static_cast<const uint16_t*>(q);
+    p.k = static_cast<const uint16_t*>(k);
+    p.v = static_cast<const uint16_t*>(v);
+    p.cu = cu_seqlens_k;
+  }
+  da_plan pl{};
+  pl.num_splits = 1;
+  pl.heads_per_tile = dp.heads_per_tile;
+  pl.tiles = B * (H_Q / dp.heads_per_tile);
+  fill_params(p, B, H_Q, H_KV, L_K_max, softmax_scale, pl);
+  p.groups = dp.groups;
+  p.mode = kFused;
+  p.out = static_cast<uint16_t*>(out);
+  p.lse = lse_out;
+  unsigned char* ws = static_cast<unsigned char*>(workspace);
+  p.o_part = reinterpret_cast<float*>(ws + wl.o_off);
+  p.m_part = reinterpret_cast<float*>(ws + wl.m_off);
+  p.l_part = reinterpret_cast<float*>(ws + wl.l_off);
+  p.arrivals = reinterpret_cast<uint32_t*>(ws + da::arrival_offset(workspace_bytes));
+  return launch_dealt(p, dp, static_cast<hipStream_t>(stream));
 }
 
 int da_split_partials(const void* q, const void* k, const void* v, const int32_t* cu_seqlens_k, float* o_part,

@@ -767,6 +767,52 @@ int make_schedule(const int32_t* seq_lens, int B, int H_Q, int H_KV, int L_K_max
   return DA_OK;
 }
 
+bool dealt_plan(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int cus, DealtPlan* out) {
+  const int g = H_Q / H_KV;
+  const int hpt = heads_per_tile(H_Q, H_KV, g > 1 ? 1 : 0);
+  const int tps = H_Q / hpt;
+  if ((int64_t)B * tps > kMaxArrivalTiles || tps > cus) return false;
+  const int groups = cus / tps;
+  if (10 * groups * tps < 9 * cus) return false;  // CUs left over
+  out->heads_per_tile = hpt;
+  out->groups = groups;
+  // K/V beyond half the MALL are streamed: they share it with whatever else
+  // the program reads before the next call.  Measured over three batches in
+  // turn, 8 KV heads: 268 MB 49.2 -> 41.0 us with the hint, 202 MB 38.4 ->
+  // 33.3, 135 MB 27.2 -> 23.1, 103 MB 28.6 -> 27.6; the same batch over and
+  // over: 41.2 -> 40.3, 31.4 -> 32.5, 23.1 -> 22.2, but 24.3 -> 26.7 at 103 MB.
+  const double most = (double)std::min<int64_t>(keys > 0 ? keys : INT64_MAX, (int64_t)B * L_K_max);
+  out->kv_nontemporal = g == hpt && most * H_KV * (2.0 * kHeadDim * 2.0) > (double)(128ll << 20) ? 1 : 0;
+  return true;
+}
+
+bool prefers_dealt(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int cus) {
+  DealtPlan dp;
+  if (L_K_max <= 0 || !dealt_plan(B, H_Q, H_KV, L_K_max, keys, cus, &dp)) return false;
+  // Measured on 240 mixed batches (1 to 128 sequences of 1 to 32768 keys, 11
+  // head shapes, equal, uniform, lognormal and bimodal lengths) against the
+  // launch with one split count: the deal costs about 8 us before and after
+  // the stream (finding it, two hand-offs, two merges), which it earns back
+  // where a workgroup's share is long, or where the longest sequence leaves
+  // other workgroups waiting.  With these lines it was taken on 30 of 114
+  // packed batches, 1.09x faster over all 114 (3.9x at most, 1.11x had the
+  // faster launch been known each time), and on 22 of 126 paged ones, 1.09x over
+  // all; 0.92x and better where it lost.
+  const bool wide = dp.heads_per_tile > 16;
+  const int64_t tps = H_Q / dp.heads_per_tile, rows = B * tps;
+  const int64_t top = (L_K_max + 31) / 32;
+  if (rows > 5 * (int64_t)cus || top < 48) return false;  // many short workgroups balance themselves
+  if (keys <= 0) {
+    // only an upper bound is known: the share has to be long were it reached
+    return (double)B * top / dp.groups >= (wide ? 128 : 64);
+  }
+  const double share = (double)std::min<int64_t>(keys / 32 + B, B * top) / dp.groups;
+  if (share >= (wide ? 128 : 32)) return true;
+  // the longest chunk of one split count against the share
+  const double longest = (double)top / (double)std::max<int64_t>(1, cus / rows);
+  return share >= (wide ? 32 : 16) && longest >= (wide ? 2.9 : 2.2) * share;
+}
+
 WorkspaceLayout workspace_layout(int B, int H_Q, int d, int s) {
   WorkspaceLayout w{};
   const size_t rows = (size_t)B * H_Q;
@@ -839,6 +885,26 @@ int da_make_schedule(const int32_t* seq_lens, int B, int H_Q, int H_KV, int L_K_
 size_t da_schedule_workspace_bytes(const da_schedule* s) {
   if (!s || s->state_rows <= 0 || s->H_Q <= 0) return 0;
   return da::workspace_layout(s->state_rows, s->H_Q, da::kHeadDim, 1).total;
+}
+
+int da_prefers_dealt(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int num_cus) {
+  if (da::check_shape(B, H_Q, H_KV, L_K_max, da::kHeadDim)) return 0;
+  if (num_cus <= 0) {
+    int is950 = 0;
+    if (da_device_info(&num_cus, &is950)) return 0;
+  }
+  return da::prefers_dealt(B, H_Q, H_KV, L_K_max, keys, num_cus) ? 1 : 0;
+}
+
+size_t da_dealt_workspace_bytes(int B, int H_Q, int H_KV, int num_cus) {
+  if (da::check_shape(B, H_Q, H_KV, 0, da::kHeadDim)) return 0;
+  if (num_cus <= 0) {
+    int is950 = 0;
+    if (da_device_info(&num_cus, &is950)) return 0;
+  }
+  da::DealtPlan dp;
+  if (!da::dealt_plan(B, H_Q, H_KV, 0, 0, num_cus, &dp)) return 0;
+  return da::workspace_layout(2 * dp.groups, H_Q, da::kHeadDim, 1).total;
 }
 
 size_t da_workspace_bytes(int B, int H_Q, int d, int num_splits) {

@@ -205,6 +205,19 @@ double schedule_time(const ScheduleModel& m, const StepCost& step, const int64_t
 int make_schedule(const int32_t* seq_lens, int B, int H_Q, int H_KV, int L_K_max, int d, int pack_gqa,
                   int num_cus, int cu_margin, int chunk_tiles, void* meta, size_t meta_bytes, da_schedule* out);
 
+// The dealt launch (dealt_kernel in decode_attn.hip): its head tile width,
+// workgroups per head tile and cache hint.
+struct DealtPlan {
+  int heads_per_tile, groups, kv_nontemporal;
+};
+// The dealt launch of a batch of `keys` keys in all (<= 0: unknown, at most B
+// * L_K_max); false (*out untouched) where the shape has more head tiles than
+// arrival counters, or head tiles that leave CUs over.
+bool dealt_plan(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int cus, DealtPlan* out);
+// Whether a batch whose lengths only the device holds is dealt rather than
+// launched with one split count for all.
+bool prefers_dealt(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int cus);
+
 // Workspace regions (256-byte aligned): chunk states Otilde | m | l from
 // offset 0 (`states` ends them), and the arrival counters of single-launch
 // merges in the last DA_ARRIVAL_BYTES of the caller's buffer, wherever its

@@ -1,0 +1,52 @@
+"""Host side of the dealt launch: where it is preferred, its workspace, and
+the argument checks that run before any device access."""
+
+import pytest
+
+import paper_2604_00028_amd as da
+from paper_2604_00028_amd import _binding as bnd
+
+FAKE = 0x100000
+
+
+def test_preferred_where_shares_are_long():
+    p = lambda *a: da.da_prefers_dealt(*a, num_cus=256)  # noqa: E731
+    assert p(32, 64, 8, 16384, 0) and p(32, 64, 8, 16384, 32 * 8000)
+    assert p(64, 8, 1, 32768, 64 * 5000)
+    assert not p(16, 32, 4, 512, 16 * 300) and not p(1, 64, 8, 8192, 8192)     # short shares
+    assert not p(32, 64, 8, 0, 0)                                              # nothing to read
+    assert not p(512, 64, 8, 8192, 0)                                          # many workgroups balance themselves
+    assert not p(8, 10, 5, 0, 0)
+    # what the Python entry points assume without asking
+    assert p(128, 64, 8, bnd.DEALT_MIN_KEYS, 0) and not p(128, 64, 8, bnd.DEALT_MIN_KEYS - 1, 0)
+    # one long sequence among short ones, the keys known or not
+    assert p(32, 64, 8, 20000, 50000) and not p(4, 64, 8, 8000, 9000)
+    # head tiles that leave more than a tenth of the CUs idle, or more than the arrival counters
+    assert not p(32, 160, 160, 16384, 0) and da.da_dealt_workspace_bytes(32, 160, 160, 256) == 0
+    assert da.da_dealt_workspace_bytes(1024, 64, 8, 256) == 0
+    assert not p(-1, 64, 8, 512, 0) and not p(4, 64, 7, 512, 0)
+
+
+def test_workspace_bytes():
+    # two chunk states for each of 256 / 8 workgroups of every head tile: Otilde | m | l, then the counters
+    assert da.da_dealt_workspace_bytes(32, 64, 8, 256) == 2 * 32 * 64 * (128 * 4 + 4 + 4) + (1 << 20)
+    assert da.da_dealt_workspace_bytes(3, 8, 1, 256) == 2 * 256 * 8 * (128 * 4 + 4 + 4) + (1 << 20)
+
+
+def call(q=FAKE, k=FAKE, v=FAKE, cu=FAKE, bt=None, sl=None, page=64, mp=8, npg=8, out=FAKE, lse=None, B=2, H_Q=8,
+         H_KV=1, L=512, d=128, ws=FAKE, ws_bytes=1 << 30):
+    return da.load().da_decode_attn_dealt(q, k, v, cu, bt, sl, page, mp, npg, out, lse, B, H_Q, H_KV, L, d, 0.0, 0,
+                                          ws, ws_bytes, None)
+
+
+@pytest.mark.parametrize("kw,code", [
+    (dict(q=None), bnd.DA_ERR_NULL), (dict(k=None), bnd.DA_ERR_NULL), (dict(out=None), bnd.DA_ERR_NULL),
+    (dict(cu=None), bnd.DA_ERR_NULL), (dict(bt=FAKE), bnd.DA_ERR_NULL),
+    (dict(q=FAKE + 8), bnd.DA_ERR_ALIGN), (dict(out=FAKE + 8), bnd.DA_ERR_ALIGN), (dict(cu=FAKE + 2), bnd.DA_ERR_ALIGN),
+    (dict(lse=FAKE + 2), bnd.DA_ERR_ALIGN), (dict(ws=FAKE + 8), bnd.DA_ERR_ALIGN),
+    (dict(d=64), bnd.DA_ERR_UNSUPPORTED), (dict(H_Q=9, H_KV=2), bnd.DA_ERR_SHAPE), (dict(L=-1), bnd.DA_ERR_SHAPE),
+    (dict(bt=FAKE, sl=FAKE, page=48), bnd.DA_ERR_UNSUPPORTED), (dict(bt=FAKE, sl=FAKE, mp=7), bnd.DA_ERR_SHAPE),
+    (dict(ws=None), bnd.DA_ERR_WORKSPACE),
+])
+def test_argument_errors(kw, code):
+    assert call(**kw) == code

@@ -1,0 +1,113 @@
+"""GPU parity of the dealt launch (da_decode_attn_dealt) against the fp64
+oracle: a batch's 32-key tiles shared evenly among the workgroups, sequences
+cut wherever a share ends and merged inside the launch.  Same bar as the other
+paths: max-abs <= 2e-2 and mean-abs <= 2e-3 on O, lse within 1e-3, bit-identical
+repeats."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_00028_amd as da
+from oracle import decode_attention
+from workloads import custom_shape, make_inputs, paged_layout
+from tests.gpu_helpers import assert_parity, dev_inputs, say, to_dev
+
+pytestmark = pytest.mark.gpu
+
+LSE_TOL = 1e-3
+
+CASES = [
+    (8, 1, [1]),                                          # one tile
+    (8, 1, [0, 0, 0]),                                    # nothing to read
+    (8, 1, [31, 32, 33, 0, 1, 64, 0]),                    # tile edges, empty sequences between
+    (64, 8, [512]),                                       # one sequence over many workgroups
+    (8, 1, [9000]),                                       # 64 pieces at most; page windows of 64 pages
+    (8, 1, [9000, 5, 0, 4100, 31]),                       # long and short in turn
+    (32, 4, [3000, 17, 0, 900, 2100, 64]),                # head, whole and tail pieces in one workgroup
+    (16, 2, [int(x) for x in np.random.default_rng(7).integers(0, 300, 200)]),   # several windows of 64 sequences
+    (16, 16, [700, 33, 1200]),                            # one head per KV head
+    (32, 1, [300, 40, 511, 2000]),                        # 32-head tiles (two column tiles, four waves)
+    (66, 2, [130, 700, 31]),                              # 33-head groups: three readers per KV head
+    (12, 4, [300, 95]),                                   # group of 3
+]
+
+
+def check(out, lse_t, O, lse, what):
+    assert_parity(out, O, what)
+    lg = lse_t.cpu().numpy().astype(np.float64)
+    fin = np.isfinite(lse)
+    assert np.array_equal(np.isfinite(lg), fin), what
+    assert np.max(np.abs(lg[fin] - lse[fin]), initial=0.0) <= LSE_TOL, what
+
+
+@pytest.mark.parametrize("page", [None, 32, 96])
+@pytest.mark.parametrize("H_Q,H_KV,lengths", CASES, ids=lambda x: str(x)[:24])
+def test_dealt_parity(H_Q, H_KV, lengths, page):
+    B = len(lengths)
+    inp = make_inputs(custom_shape(B, H_Q, H_KV, max(lengths), varlen=True), seed=B + H_Q, lengths=lengths)
+    O, lse = decode_attention(inp.q, inp.k, inp.v, inp.lengths, inp.cu_seqlens_k)
+    q, k, v, cu = dev_inputs(inp)
+    kw = dict(cu_seqlens_k=cu)
+    if page is not None:
+        pg = paged_layout(inp, page, seed=page + 3)
+        k, v = to_dev(pg.k_cache), to_dev(pg.v_cache)
+        kw = dict(block_table=torch.from_numpy(pg.block_table).cuda(), seq_lens=torch.from_numpy(pg.seq_lens).cuda())
+    ws = torch.zeros(da.da_dealt_workspace_bytes(B, H_Q, H_KV), dtype=torch.uint8, device="cuda")
+    first = None
+    for r in range(3):
+        say(f"dealt B{B} {H_Q}/{H_KV} {str(lengths)[:40]} page={page} run {r}")
+        ws[:-(1 << 20)].fill_(255)      # chunk states need no initialisation (NaN bits here)
+        lse_t = torch.empty(B, H_Q, dtype=torch.float32, device="cuda")
+        out = da.da_decode_attn_dealt(q, k, v, max(lengths), lse_out=lse_t, workspace=ws, **kw)
+        torch.cuda.synchronize()
+        check(out, lse_t, O, lse, f"dealt {H_Q}/{H_KV} page={page}")
+        assert int(ws[-(1 << 20):].max()) == 0      # the arrival counters are back at zero
+        first = first or (out, lse_t)
+        assert torch.equal(out.view(torch.int16), first[0].view(torch.int16)) and torch.equal(lse_t, first[1])
+
+
+@pytest.mark.parametrize("page", [None, 64])
+def test_planning_entries_deal_a_mixed_batch(page):
+    """da_decode_attn and da_decode_attn_paged give the dealt launch's bits
+    where it is preferred, also from a graph whose lengths change between
+    replays, and their own plan's with a forced split count."""
+    H_Q, H_KV = 64, 8
+    lengths = [int(x) for x in np.random.default_rng(3).integers(1500, 6000, 16)]
+    B, top = len(lengths), 8000
+    assert da.da_prefers_dealt(B, H_Q, H_KV, top, 0) and da.da_prefers_dealt(B, H_Q, H_KV, top, sum(lengths))
+    inp = make_inputs(custom_shape(B, H_Q, H_KV, max(lengths), varlen=True), seed=11, lengths=lengths)
+    q, k, v, cu = dev_inputs(inp)
+    if page is None:
+        call = lambda s: da.da_decode_attn(q, k, v, cu, L_K_max=top, num_splits=s)  # noqa: E731
+        dealt = lambda: da.da_decode_attn_dealt(q, k, v, top, cu)  # noqa: E731
+    else:
+        pg = paged_layout(inp, page, seed=5, max_pages=-(-top // page))
+        k, v = to_dev(pg.k_cache), to_dev(pg.v_cache)
+        bt, sl = torch.from_numpy(pg.block_table).cuda(), torch.from_numpy(pg.seq_lens).cuda()
+        call = lambda s: da.da_decode_attn_paged(q, k, v, bt, sl, top, num_splits=s)  # noqa: E731
+        dealt = lambda: da.da_decode_attn_dealt(q, k, v, top, block_table=bt, seq_lens=sl)  # noqa: E731
+    say(f"dealt route page={page}")
+    a, b, forced = call(0), dealt(), call(2)
+    torch.cuda.synchronize()
+    assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    picks = [0, int(np.argmax(lengths)), 9]
+    cuh = inp.cu_seqlens_k
+    for s in picks:
+        O, _ = decode_attention(inp.q[s:s + 1], inp.k[cuh[s]:cuh[s + 1]][None], inp.v[cuh[s]:cuh[s + 1]][None])
+        assert_parity(a[s:s + 1], O, f"dealt route sequence {s}")
+        assert_parity(forced[s:s + 1], O, f"forced splits sequence {s}")
+    if page is None:
+        return
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        call(0)                         # workspace of this stream
+    stream.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        got = call(0)
+    for r in range(4):
+        sl.copy_(torch.from_numpy(pg.seq_lens) - 37 * r)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got.view(torch.int16), dealt().view(torch.int16)), f"replay {r}"
