@@ -11,7 +11,7 @@ from __future__ import annotations
 
 import ctypes
 import os
-from typing import Dict, List, Optional, Sequence, Tuple
+from typing import Callable, Dict, List, Optional, Sequence, Tuple
 
 import torch
 
@@ -236,25 +236,44 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None or t.numel() == 0 else t.data_ptr()
 
 
+# The handle of a device's current stream without a Stream object around it (0.1 us instead of 1.9).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(dev: torch.device, stream) -> int:
     if stream is None:
+        if _raw_stream is not None and dev.index is not None:
+            return _raw_stream(dev.index)
         return torch.cuda.current_stream(dev).cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
+def _new_out(q: torch.Tensor) -> torch.Tensor:
+    return torch.empty_like(q, memory_format=torch.contiguous_format)
+
+
+def _bf16_cuda(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, names=("q", "k", "v")) -> None:
+    bf16 = torch.bfloat16
+    if (q.dtype is bf16 and k.dtype is bf16 and v.dtype is bf16 and q.is_contiguous() and k.is_contiguous()
+            and v.is_contiguous() and q.is_cuda and k.is_cuda and v.is_cuda):
+        return
+    for name, t in zip(names, (q, k, v)):
+        if t.dtype != bf16 or not t.is_contiguous() or not t.is_cuda:
+            raise ValueError(f"{name} must be a contiguous bfloat16 CUDA tensor")
+
+
 def _shapes(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, cu: Optional[torch.Tensor],
             L_K_max: Optional[int]) -> Tuple[int, int, int, int, int]:
-    for name, t in (("q", q), ("k", k), ("v", v)):
-        if t.dtype != torch.bfloat16 or not t.is_contiguous() or not t.is_cuda:
-            raise ValueError(f"{name} must be a contiguous bfloat16 CUDA tensor")
-    if k.shape != v.shape:
+    _bf16_cuda(q, k, v)
+    ks = k.shape
+    if ks != v.shape:
         raise ValueError("k and v shapes differ")
     B, H_Q, d = q.shape
     if cu is None:
-        if k.dim() != 4 or k.shape[0] != B or k.shape[3] != d:
+        if len(ks) != 4 or ks[0] != B or ks[3] != d:
             raise ValueError("k must be [B, L_K, H_KV, d]")
-        L = k.shape[1]
-        H_KV = k.shape[2]
+        L = ks[1]
+        H_KV = ks[2]
         if L_K_max is not None and L_K_max != L:
             raise ValueError("L_K_max must equal k.shape[1] for the fixed layout")
         L_K_max = L
@@ -299,6 +318,21 @@ def workspace_for(dev: torch.device, stream_handle: int, nbytes: int) -> torch.T
     return ws
 
 
+def _planned_inside(call, dev: torch.device, s_handle: int, workspace: Optional[torch.Tensor],
+                    need: Callable[[], int]) -> None:
+    """Run an entry point that plans for itself: call(workspace pointer,
+    bytes) returns its status.  Without a workspace of the caller's, the one
+    cached for this stream is offered as it is; only where the plan needs a
+    larger one (which the entry point finds before it launches anything) is the
+    plan made here too, for need()'s bytes."""
+    ws = workspace if workspace is not None else _workspaces.get((dev.index, s_handle))
+    rc = call(_ptr(ws), ws.numel() * ws.element_size() if ws is not None else 0)
+    if rc == DA_ERR_WORKSPACE and workspace is None:
+        ws = workspace_for(dev, s_handle, need())
+        rc = call(_ptr(ws), ws.numel() * ws.element_size())
+    _check(rc)
+
+
 def da_decode_attn(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, cu_seqlens_k: Optional[torch.Tensor] = None,
                    out: Optional[torch.Tensor] = None, lse_out: Optional[torch.Tensor] = None, *,
                    L_K_max: Optional[int] = None, softmax_scale: float = 0.0, num_splits: int = 0,
@@ -312,18 +346,14 @@ def da_decode_attn(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, cu_seqlens
                                     stream=stream)
     dev = q.device
     if out is None:
-        out = torch.empty((B, H_Q, d), dtype=torch.bfloat16, device=dev)
+        out = _new_out(q)
     s_handle = _stream(dev, stream)
-    if workspace is None:
-        plan = da_make_plan(B, H_Q, H_KV, L, d, num_splits, pack_gqa)
-        nbytes = da_workspace_bytes(B, H_Q, d, plan.num_splits)
-        if nbytes:
-            workspace = workspace_for(dev, s_handle, nbytes)
-    ws_ptr = _ptr(workspace)
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    _check(load().da_decode_attn(_ptr(q), _ptr(k), _ptr(v), _ptr(cu_seqlens_k), _ptr(out), _ptr(lse_out),
-                                 B, H_Q, H_KV, L, d, float(softmax_scale), int(num_splits), int(pack_gqa),
-                                 ws_ptr, ws_bytes, s_handle))
+    _planned_inside(
+        lambda ws, n: load().da_decode_attn(_ptr(q), _ptr(k), _ptr(v), _ptr(cu_seqlens_k), _ptr(out), _ptr(lse_out),
+                                            B, H_Q, H_KV, L, d, float(softmax_scale), int(num_splits), int(pack_gqa),
+                                            ws, n, s_handle),
+        dev, s_handle, workspace,
+        lambda: da_workspace_bytes(B, H_Q, d, da_make_plan(B, H_Q, H_KV, L, d, num_splits, pack_gqa).num_splits))
     return out
 
 
@@ -337,7 +367,7 @@ def da_decode_attn_planned(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, pl
     B, H_Q, H_KV, L, d = _shapes(q, k, v, cu_seqlens_k, L_K_max)
     dev = q.device
     if out is None:
-        out = torch.empty((B, H_Q, d), dtype=torch.bfloat16, device=dev)
+        out = _new_out(q)
     s_handle = _stream(dev, stream)
     if workspace is None:
         nbytes = da_workspace_bytes(B, H_Q, d, plan.num_splits)
@@ -361,7 +391,7 @@ def da_decode_attn_noalloc(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
     nothing at all."""
     B, H_Q, H_KV, L, d = _shapes(q, k, v, cu_seqlens_k, L_K_max)
     if out is None:
-        out = torch.empty((B, H_Q, d), dtype=torch.bfloat16, device=q.device)
+        out = _new_out(q)
     _check(load().da_decode_attn_noalloc(_ptr(q), _ptr(k), _ptr(v), _ptr(cu_seqlens_k), _ptr(out), _ptr(lse_out),
                                          B, H_Q, H_KV, L, d, float(softmax_scale), int(num_splits), int(pack_gqa),
                                          _stream(q.device, stream)))
@@ -370,9 +400,7 @@ def da_decode_attn_noalloc(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
 
 def _paged_args(q, k_cache, v_cache, block_table, seq_lens):
     """Check a paged call's tensors; (B, H_Q, H_KV, d, page_size, max_pages, num_pages)."""
-    for name, t in (("q", q), ("k_cache", k_cache), ("v_cache", v_cache)):
-        if t.dtype != torch.bfloat16 or not t.is_contiguous() or not t.is_cuda:
-            raise ValueError(f"{name} must be a contiguous bfloat16 CUDA tensor")
+    _bf16_cuda(q, k_cache, v_cache, ("q", "k_cache", "v_cache"))
     for name, t in (("block_table", block_table), ("seq_lens", seq_lens)):
         if t.dtype != torch.int32 or not t.is_contiguous() or not t.is_cuda:
             raise ValueError(f"{name} must be a contiguous int32 CUDA tensor")
@@ -400,18 +428,16 @@ def da_decode_attn_paged(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.
                                     softmax_scale=softmax_scale, stream=stream)
     dev = q.device
     if out is None:
-        out = torch.empty((B, H_Q, d), dtype=torch.bfloat16, device=dev)
+        out = _new_out(q)
     s_handle = _stream(dev, stream)
-    if workspace is None:
-        plan = da_make_plan(B, H_Q, H_KV, int(L_K_max), d, num_splits, pack_gqa)
-        nbytes = da_workspace_bytes(B, H_Q, d, plan.num_splits)
-        if nbytes:
-            workspace = workspace_for(dev, s_handle, nbytes)
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    _check(load().da_decode_attn_paged(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table), _ptr(seq_lens),
-                                       _ptr(out), _ptr(lse_out), B, H_Q, H_KV, page_size, max_pages, num_pages,
-                                       int(L_K_max), d, float(softmax_scale), int(num_splits), int(pack_gqa),
-                                       _ptr(workspace), ws_bytes, s_handle))
+    L = int(L_K_max)
+    _planned_inside(
+        lambda ws, n: load().da_decode_attn_paged(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table),
+                                                  _ptr(seq_lens), _ptr(out), _ptr(lse_out), B, H_Q, H_KV, page_size,
+                                                  max_pages, num_pages, L, d, float(softmax_scale), int(num_splits),
+                                                  int(pack_gqa), ws, n, s_handle),
+        dev, s_handle, workspace,
+        lambda: da_workspace_bytes(B, H_Q, d, da_make_plan(B, H_Q, H_KV, L, d, num_splits, pack_gqa).num_splits))
     return out
 
 
@@ -424,7 +450,7 @@ def da_decode_attn_paged_planned(q: torch.Tensor, k_cache: torch.Tensor, v_cache
     B, H_Q, H_KV, d, page_size, max_pages, num_pages = _paged_args(q, k_cache, v_cache, block_table, seq_lens)
     dev = q.device
     if out is None:
-        out = torch.empty((B, H_Q, d), dtype=torch.bfloat16, device=dev)
+        out = _new_out(q)
     s_handle = _stream(dev, stream)
     if workspace is None:
         nbytes = da_workspace_bytes(B, H_Q, d, plan.num_splits)
@@ -475,9 +501,7 @@ def da_decode_attn_scheduled(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, 
     Contiguous K/V (fixed, or varlen with cu_seqlens_k) when block_table is
     None, else paged: k, v [num_pages, page_size, H_KV, d] with block_table
     [B, max_pages] and seq_lens [B]."""
-    for name, t in (("q", q), ("k", k), ("v", v)):
-        if t.dtype != torch.bfloat16 or not t.is_contiguous() or not t.is_cuda:
-            raise ValueError(f"{name} must be a contiguous bfloat16 CUDA tensor")
+    _bf16_cuda(q, k, v)
     if meta_dev.dtype != torch.uint8 or not meta_dev.is_cuda or meta_dev.numel() < sched.meta_bytes:
         raise ValueError("meta_dev must be a CUDA uint8 tensor holding the schedule's metadata")
     B, H_Q, d = q.shape
@@ -492,7 +516,7 @@ def da_decode_attn_scheduled(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, 
         max_pages = block_table.shape[1]
     dev = q.device
     if out is None:
-        out = torch.empty((B, H_Q, d), dtype=torch.bfloat16, device=dev)
+        out = _new_out(q)
     s_handle = _stream(dev, stream)
     if workspace is None:
         nbytes = da_schedule_workspace_bytes(sched)
@@ -526,7 +550,7 @@ def da_decode_attn_dealt(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, L_K_
         L = int(L_K_max)
     dev = q.device
     if out is None:
-        out = torch.empty((B, H_Q, d), dtype=torch.bfloat16, device=dev)
+        out = _new_out(q)
     s_handle = _stream(dev, stream)
     if workspace is None:
         workspace = workspace_for(dev, s_handle, da_dealt_workspace_bytes(B, H_Q, H_KV))

@@ -63,8 +63,16 @@ const CostModel& mi355x_model() {
 // reflects that a CU's tile loop slows as the chip nears its HBM rate.  The
 // two-wave launch (group_waves) is a measured rule applied after the model
 // has chosen; the model prices the four-wave launch.
+//
+// `beat`: the caller only asks whether T is below it.  A lower bound of T that
+// takes no pow settles most of those questions: with mx and mn the larger and
+// smaller of the two bounds, x = (mn / mx)^4 <= (mn / mx)^p for p <= 4, and
+// (1 + x)^(1/p) >= 1 + (2^(1/4) - 1) x on [0, 1] (a concave function lies above
+// its chord, and 2^(1/p) >= 2^(1/4)).  It is returned instead when it is not
+// below `beat`.  A plan tries up to 384 launches: 3.8-9.1 us with two pows
+// each, 0.3-1 us with this bound and the end of the search below.
 double model_time(const CostModel& m, int B, int H_Q, int H_KV, int L_K, int hpt, int s, int cus, int vs,
-                  bool fused) {
+                  bool fused, double beat) {
   const int wide = hpt > 16 ? 1 : 0;
   const double row_bytes = 2.0 * kHeadDim * 2.0;  // K and V row of one KV head
   const int64_t tiles = (int64_t)B * H_Q / hpt;
@@ -79,8 +87,14 @@ double model_time(const CostModel& m, int B, int H_Q, int H_KV, int L_K, int hpt
   double bytes = (double)B * L_K * H_KV * row_bytes;
   if (s > 1) bytes += 2.0 * s * (double)B * H_Q * (kHeadDim + 2) * 4.0;
   const double stream = m.hbm0 + bytes / m.hbm_rate;
-  double t = pow(pow(compute, m.pnorm) + pow(stream, m.pnorm), 1.0 / m.pnorm);
-  return t + merge_time(m, hpt, s, fused);
+  const double merge = merge_time(m, hpt, s, fused);
+  if (beat < INFINITY && m.pnorm <= 4.0) {
+    const double mx = std::max(compute, stream), r = std::min(compute, stream) / mx;
+    // rounded down by more than the pows below can be off
+    const double least = (mx * (1.0 + 0.189 * (r * r) * (r * r)) + merge) * (1.0 - 1e-12);
+    if (least >= beat) return least;
+  }
+  return pow(pow(compute, m.pnorm) + pow(stream, m.pnorm), 1.0 / m.pnorm) + merge;
 }
 
 // The merge of s > 1 chunk states: a second launch, merge0 + merge1 s; or
@@ -145,16 +159,23 @@ bool fused_merge(const CostModel& m, int hpt, int s, int64_t tiles) {
 // that the slices' repeated K reads stay there; the slice factors were
 // measured on such calls) and the model puts them at least 1% ahead of one
 // slice; *t gets the modelled time.
+// `beat`: as for model_time; *t is at least `beat` where no slice count is below it.
 static int best_vslices(const CostModel& m, int B, int H_Q, int H_KV, int L_K, int hpt, int s, int cus, bool slices,
-                        double* t) {
+                        double* t, double beat = INFINITY) {
   const int64_t tiles = (int64_t)B * H_Q / hpt;
   const bool fused = fused_merge(m, hpt, s, tiles);
-  const double one = model_time(m, B, H_Q, H_KV, L_K, hpt, s, cus, 1, fused);
+  double one = model_time(m, B, H_Q, H_KV, L_K, hpt, s, cus, 1, fused, beat);
+  bool exact = one < beat || beat == INFINITY;
   int best_vs = 1;
   double best = one;
   slices = slices && (double)B * L_K * H_KV * (2.0 * kHeadDim * 2.0) <= (double)kSliceKvBytes;
   for (int vs = 2; slices && vs <= 4 && launch_grid(tiles * s, vs) <= cus; vs *= 2) {
-    const double tv = model_time(m, B, H_Q, H_KV, L_K, hpt, s, cus, vs, fused);
+    const double tv = model_time(m, B, H_Q, H_KV, L_K, hpt, s, cus, vs, fused, beat);
+    if (tv >= beat) continue;
+    if (!exact) {
+      best = one = model_time(m, B, H_Q, H_KV, L_K, hpt, s, cus, 1, fused);
+      exact = true;
+    }
     if (tv < best && tv < kSplitGain * one) {
       best = tv;
       best_vs = vs;
@@ -176,9 +197,13 @@ static int mi355x_splits(const CostModel& m, int B, int H_Q, int H_KV, int L_K, 
   best_vslices(m, B, H_Q, H_KV, L_K, hpt, 1, cus, slices, &one);
   int best_s = 1;
   double best = one;
+  const int64_t tiles = (int64_t)B * H_Q / hpt;
   for (int s = 2; s <= kMaxSplits; ++s) {
+    // No launch is faster than its fixed part and its merge, and neither
+    // merge gets cheaper with more chunks: past that the search is over.
+    if ((m.base[hpt > 16 ? 1 : 0] + merge_time(m, hpt, s, fused_merge(m, hpt, s, tiles))) * (1.0 - 1e-12) >= best) break;
     double ts = 0.0;
-    best_vslices(m, B, H_Q, H_KV, L_K, hpt, s, cus, slices, &ts);
+    best_vslices(m, B, H_Q, H_KV, L_K, hpt, s, cus, slices, &ts, best);
     if (ts < best) {
       best = ts;
       best_s = s;

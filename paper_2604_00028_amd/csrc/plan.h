@@ -2,6 +2,7 @@
 // policy, the sequence partition and workspace sizing.  No HIP calls here.
 #pragma once
 
+#include <math.h>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -70,7 +71,7 @@ constexpr double kSplitGain = 0.99;
 // the chunk states are merged inside the split launch (da_plan.combine 1)
 // rather than by a second launch.
 double model_time(const CostModel& m, int B, int H_Q, int H_KV, int L_K, int hpt, int s, int cus, int vs = 1,
-                  bool fused = false);
+                  bool fused = false, double beat = INFINITY);
 
 // Chunk states the merging workgroup of a single-launch merge loads at once
 // (16-column / 32-column head tiles): one batch is merged in registers, more
