@@ -153,11 +153,11 @@ struct Params {
   const int32_t* work;  // nullable: per-sequence schedule, int32x4 {tile, first, end, state row} per workgroup
   const int32_t* seqs;  // schedule, kFused: int32x2 [B] {first chunk-state row or -1, chunk count}
   int state_rows;       // chunk-state rows of the schedule
-  int groups;           // dealt launch: workgroups per head tile
   int B, H_Q, H_KV, L_K, g, hpt, tiles_per_seq, tiles, s, mode;
   int xcd_group;        // 1: consecutive tiles share an XCD (packing off)
   Div div_s, div_tps, div_g;  // s, tiles_per_seq, g
   float scale_log2;     // softmax scale * log2(e)
+  int groups;           // dealt launch: workgroups per head tile
 };
 
 // Max and sum over lanes {l, l^16, l^32, l^48}: the 4 row groups of one MFMA
@@ -294,59 +294,44 @@ __device__ __forceinline__ void merge_rows(const float* o_part, const float* m_p
 
 // The single-launch merge: the last workgroup of a tile merges the tile's
 // s chunk states for its hpt <= 32 rows (query heads), with every thread
-// holding float4 output columns.  Chunk i of the tile's head h is state row
-// srow0 + i * cstride + h (state_rows rows in all); its output row is orow0
-// + h; with FIRST, chunk 0 sits first_rows further on.  The states were written in this launch by
-// other workgroups with device-scope stores and are read with device-scope
-// loads.  Per output element the operations and their order are those of
-// merge_rows (maximum over non-empty chunks, then the weights, L and O
-// accumulated in chunk order), so both merges give the same bits.  The
-// code is kept short and rolled: it runs once per tile, on cold
-// instruction caches.  `lds` holds at least 3 x 64 x 32 floats.
-template <int NT, int W, bool FIRST = false>
-__device__ __forceinline__ void merge_tile(const Params& p, float* lds, int64_t srow0, int64_t cstride, int s,
-                                           int64_t orow0, int64_t state_rows, int tid, uint32_t first_rows = 0) {
-  constexpr int T = 64 * W;              // threads
-  constexpr int R = T / 32;              // thread t stages row t % 32 of chunks t / 32 + R u
-  constexpr int IPT = NT * 16 * 32 / T;  // float4 columns per thread (hpt * 32 items over T threads)
-  constexpr int CB = da::kFusedBatch[NT - 1];  // chunks of columns loaded at once
-  constexpr uint32_t kOut = 0xfffffff0u; // an offset past every buffer: reads zero, touches nothing
+// holding J float4 output columns, CB chunks of each at once: column item tid + T j is row item / 32,
+// float4 column item % 32.  Chunk i of the tile's head h is state row srow0 +
+// i * cstride + h; with FIRST, chunk 0 sits first_rows further on.  Its output
+// row is orow0 + h.  The states were written in this launch by other
+// workgroups with device-scope stores and are read with device-scope loads.
+// Per output element the operations and their order are those of merge_rows
+// (maximum over non-empty chunks, then the weights, L and O accumulated in
+// chunk order), so both merges give the same bits.
+//
+// Bound by latency: one trip to memory for up to CB chunks (all loads in
+// flight at once), and the code's own fetch, since it runs once per launch on
+// cold instruction caches.  So the loads carry no per-lane guard: the buffer
+// ranges start at the tile's first state row and end with chunk s - 1, what is
+// read past either is never used, and rows past hpt read other heads' states,
+// which are not stored.  s <= CB merges in registers; more chunks stage their
+// maxima and sums in `lds` (at least 2 x (64 + 16) x 32 + 8 x 32 floats) and
+// take the columns in batches of CB.
+template <int W, int J, int CB, bool FIRST>
+__device__ __forceinline__ void merge_columns(const Params& p, float* lds, int64_t srow0, int64_t cstride, int s,
+                                              int64_t orow0, int tid, uint32_t first_rows) {
+  constexpr int T = 64 * W;    // threads
+  constexpr int R = T / 32;    // thread t stages row t % 32 of chunks t / 32 + R u
   const int hpt = p.hpt;
-  // 32-bit offsets: the chunk states of a call stay below 2 GiB (checked on the host), and the
-  // buffer ranges end with them, so out-of-range rows and chunks read as zeros
+  // 32-bit offsets: the chunk states of a call stay below 2 GiB (checked on the host)
   const uint32_t rows = (uint32_t)cstride;  // state rows between two chunks of one head
-  const uint32_t r0 = (uint32_t)srow0;
-  const uint32_t nrows = (uint32_t)state_rows;
-  const __amdgpu_buffer_rsrc_t mrs = make_rsrc(p.m_part, nrows * 4u);
-  const __amdgpu_buffer_rsrc_t lrs = make_rsrc(p.l_part, nrows * 4u);
-  const __amdgpu_buffer_rsrc_t ors = make_rsrc(p.o_part, nrows * (uint32_t)D * 4u);
-  // chunk rows are padded to 64 + CB so that a batch reads them unconditionally
-  float* lm = lds;                               // [64 + CB chunks][32 rows] maxima
-  float* ll = lds + (DA_MAX_SPLITS + CB) * 32;   // [64 + CB][32] sums
-  float* lp = ll + (DA_MAX_SPLITS + CB) * 32;    // [R][32] maxima over each thread's live chunks
-  // column items of this thread: item tid + T j is row item / 32, float4 column item % 32
-  uint32_t ooff[IPT];
+  const uint32_t span = (uint32_t)(s - 1) * rows + (uint32_t)hpt + (FIRST && s == 1 ? first_rows : 0u);
+  const __amdgpu_buffer_rsrc_t mrs = make_rsrc(p.m_part + srow0, span * 4u);
+  const __amdgpu_buffer_rsrc_t lrs = make_rsrc(p.l_part + srow0, span * 4u);
+  const __amdgpu_buffer_rsrc_t ors = make_rsrc(p.o_part + srow0 * D, span * (uint32_t)D * 4u);
+  auto chunk_row = [&](int i) { return (uint32_t)i * rows + (FIRST && i == 0 ? first_rows : 0u); };
+  auto load_cols = [&](f32x4 (&a)[J][CB], int i0) {
 #pragma unroll
-  for (int j = 0; j < IPT; ++j) {
-    const uint32_t item = (uint32_t)(tid + T * j), h = item >> 5, c = item & 31u;
-    ooff[j] = h < (uint32_t)hpt ? ((r0 + h) * D + 4u * c) * 4u : kOut;
-  }
-  const uint32_t ostride = rows * (uint32_t)D * 4u;  // bytes between two chunks of one row
-  f32x4 a[IPT][CB];
-  const int items = hpt * 32;  // column items of the tile; item groups j with T j >= items are skipped
-  auto load_cols = [&](int i0) {
+    for (int u = 0; u < CB; ++u)
 #pragma unroll
-    for (int j = 0; j < IPT; ++j)
-#pragma unroll
-      for (int u = 0; u < CB; ++u)
-        if (T * j < items && i0 + u < s)  // uniform
+      for (int j = 0; j < J; ++j)
         a[j][u] = __builtin_bit_cast(
             f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                       ors,
-                       ooff[j] != kOut
-                           ? ooff[j] + (uint32_t)(i0 + u) * ostride + (FIRST && i0 + u == 0 ? first_rows * D * 4u : 0u)
-                           : kOut,
-                       0, kDeviceScope));
+                       ors, (uint32_t)(tid + T * j) * 16u + chunk_row(i0 + u) * (uint32_t)D * 4u, 0, kDeviceScope));
   };
   auto store_item = [&](int j, float M, float L, const f32x4& o) {
     const int item = tid + T * j, h = item >> 5, c = item & 31;
@@ -357,114 +342,125 @@ __device__ __forceinline__ void merge_tile(const Params& p, float* lds, int64_t 
         make_uint2(pack_bf16x2(o[0] * inv, o[1] * inv), pack_bf16x2(o[2] * inv, o[3] * inv));
     if (p.lse && c == 0) p.lse[row] = L > 0.f ? M + logf(L) : -INFINITY;
   };
-  if (s <= CB) {
-    // one batch: every thread loads the maxima and sums of its own rows'
-    // chunks with its columns and merges in registers (no LDS, no barrier)
-    load_cols(0);
-    float bm[IPT][CB], bl[IPT][CB];
+  float M[J], L[J];
+  f32x4 o[J];
 #pragma unroll
-    for (int j = 0; j < IPT; ++j) {
-      const uint32_t h = (uint32_t)(tid + T * j) >> 5;
-      const uint32_t moff = h < (uint32_t)hpt ? (r0 + h) * 4u : kOut;
-#pragma unroll
-      for (int u = 0; u < CB; ++u) {  // chunks past s read as l = 0, never live
-        const uint32_t off =
-            moff != kOut && u < s ? moff + (uint32_t)u * rows * 4u + (FIRST && u == 0 ? first_rows * 4u : 0u) : kOut;
-        bm[j][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(mrs, off, 0, kDeviceScope));
-        bl[j][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(lrs, off, 0, kDeviceScope));
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < IPT; ++j) {
-      if (T * j >= items) break;  // uniform
-      float M = -INFINITY, L = 0.f;
-      f32x4 o = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int u = 0; u < CB; ++u) M = bl[j][u] > 0.f ? fmaxf(M, bm[j][u]) : M;
-#pragma unroll
-      for (int u = 0; u < CB; ++u) {
-        if (u < s) {
-          const bool live = bl[j][u] > 0.f;
-          const float w = live ? __builtin_amdgcn_exp2f((bm[j][u] - M) * kLog2e) : 0.f;
-          L = fmaf(w, bl[j][u], L);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = fmaf(w, a[j][u][e], o[e]);
-        }
-      }
-      store_item(j, M, L, o);
-    }
-    return;
-  }
-  {
-    const uint32_t h = (uint32_t)tid & 31u;
-    const int i0 = tid >> 5;
-    const uint32_t moff = h < (uint32_t)hpt ? (r0 + h) * 4u : kOut;
-    float mv[DA_MAX_SPLITS / R], lv[DA_MAX_SPLITS / R];
-#pragma unroll
-    for (int u = 0; u < DA_MAX_SPLITS / R; ++u) {
-      if (R * u >= s) break;  // uniform
-      const int i = i0 + R * u;
-      const uint32_t off =
-          moff != kOut && i < s ? moff + (uint32_t)i * rows * 4u + (FIRST && i == 0 ? first_rows * 4u : 0u) : kOut;
-      mv[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(mrs, off, 0, kDeviceScope));
-      lv[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(lrs, off, 0, kDeviceScope));
-    }
-    load_cols(0);  // in flight while the maxima are staged
-    float pm = -INFINITY;
-#pragma unroll
-    for (int u = 0; u < DA_MAX_SPLITS / R; ++u) {
-      if (R * u >= s) break;
-      const int i = i0 + R * u;  // < 64; rows and chunks out of range read as l = 0, never live
-      lm[i * 32 + h] = mv[u];
-      ll[i * 32 + h] = lv[u];
-      pm = lv[u] > 0.f ? fmaxf(pm, mv[u]) : pm;
-    }
-    lp[i0 * 32 + h] = pm;
-  }
-  __syncthreads();
-  float M[IPT], L[IPT];
-  f32x4 o[IPT];
-  int hh[IPT];
-#pragma unroll
-  for (int j = 0; j < IPT; ++j) {
-    hh[j] = ((tid + T * j) >> 5) & 31;
+  for (int j = 0; j < J; ++j) {
     M[j] = -INFINITY;
-#pragma unroll
-    for (int r = 0; r < R; ++r) M[j] = fmaxf(M[j], lp[r * 32 + hh[j]]);
     L[j] = 0.f;
     o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  for (int i0 = 0; i0 < s; i0 += CB) {
-    if (i0 > 0) load_cols(i0);
-    // the batch's maxima and sums, read at once (rows past s are read, never used)
-    float bm[IPT][CB], bl[IPT][CB];
-#pragma unroll
-    for (int j = 0; j < IPT; ++j)
-#pragma unroll
-      for (int u = 0; u < CB; ++u) {
-        bm[j][u] = lm[(i0 + u) * 32 + hh[j]];
-        bl[j][u] = ll[(i0 + u) * 32 + hh[j]];
-      }
+  // chunks [i0, min(i0 + CB, s)) with maxima bm and sums bl
+  auto add = [&](const f32x4 (&a)[J][CB], const float (&bm)[J][CB], const float (&bl)[J][CB], int i0) {
 #pragma unroll
     for (int u = 0; u < CB; ++u) {
-      if (i0 + u < s) {
+      if (i0 + u < s) {  // uniform
 #pragma unroll
-        for (int j = 0; j < IPT; ++j) {
-          if (T * j >= items) break;  // uniform
-          const float mi = bm[j][u], li = bl[j][u];
-          const bool live = li > 0.f;
-          const float w = live ? __builtin_amdgcn_exp2f((mi - M[j]) * kLog2e) : 0.f;
-          L[j] = fmaf(w, li, L[j]);
+        for (int j = 0; j < J; ++j) {
           // an empty chunk's output is exactly zero here (w = 0 and O~ = 0 add nothing), as the
           // combine's guard on empty chunks makes it
+          const float w = bl[j][u] > 0.f ? __builtin_amdgcn_exp2f((bm[j][u] - M[j]) * kLog2e) : 0.f;
+          L[j] = fmaf(w, bl[j][u], L[j]);
 #pragma unroll
           for (int e = 0; e < 4; ++e) o[j][e] = fmaf(w, a[j][u][e], o[j][e]);
         }
       }
     }
+  };
+  f32x4 a[J][CB];
+  float bm[J][CB], bl[J][CB];
+  if (s <= CB) {
+    // one batch: every thread loads its own rows' maxima and sums with its columns
+#pragma unroll
+    for (int u = 0; u < CB; ++u)
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const uint32_t off = ((uint32_t)((tid + T * j) >> 5) + chunk_row(u)) * 4u;
+        bm[j][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(mrs, off, 0, kDeviceScope));
+        bl[j][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(lrs, off, 0, kDeviceScope));
+      }
+    load_cols(a, 0);
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+      for (int u = 0; u < CB; ++u) M[j] = u < s && bl[j][u] > 0.f ? fmaxf(M[j], bm[j][u]) : M[j];
+    add(a, bm, bl, 0);
+  } else {
+    // chunk rows are padded to 64 + CB so that a batch reads them unconditionally
+    float* lm = lds;                               // [64 + CB chunks][32 rows] maxima
+    float* ll = lds + (DA_MAX_SPLITS + CB) * 32;   // [64 + CB][32] sums
+    float* lp = ll + (DA_MAX_SPLITS + CB) * 32;    // [R][32] maxima over each thread's live chunks
+    {
+      const uint32_t h = (uint32_t)tid & 31u;
+      const int i0 = tid >> 5;
+      float mv[DA_MAX_SPLITS / R], lv[DA_MAX_SPLITS / R];
+#pragma unroll
+      for (int u = 0; u < DA_MAX_SPLITS / R; ++u) {
+        if (R * u >= s) break;  // uniform
+        const uint32_t off = (chunk_row(i0 + R * u) + h) * 4u;
+        mv[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(mrs, off, 0, kDeviceScope));
+        lv[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(lrs, off, 0, kDeviceScope));
+      }
+      load_cols(a, 0);  // in flight while the maxima are staged
+      float pm = -INFINITY;
+#pragma unroll
+      for (int u = 0; u < DA_MAX_SPLITS / R; ++u) {
+        if (R * u >= s) break;
+        const int i = i0 + R * u;  // < 64; rows past s are never used
+        lm[i * 32 + h] = mv[u];
+        ll[i * 32 + h] = lv[u];
+        pm = i < s && lv[u] > 0.f ? fmaxf(pm, mv[u]) : pm;
+      }
+      lp[i0 * 32 + h] = pm;
+    }
+    __syncthreads();
+    int hh[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      hh[j] = ((tid + T * j) >> 5) & 31;
+#pragma unroll
+      for (int r = 0; r < R; ++r) M[j] = fmaxf(M[j], lp[r * 32 + hh[j]]);
+    }
+    for (int i0 = 0; i0 < s; i0 += CB) {
+      if (i0 > 0) load_cols(a, i0);
+      // the batch's maxima and sums, read at once (rows past s are read, never used)
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+#pragma unroll
+        for (int u = 0; u < CB; ++u) {
+          bm[j][u] = lm[(i0 + u) * 32 + hh[j]];
+          bl[j][u] = ll[(i0 + u) * 32 + hh[j]];
+        }
+      add(a, bm, bl, i0);
+    }
   }
 #pragma unroll
-  for (int j = 0; j < IPT; ++j) store_item(j, M[j], L[j], o[j]);
+  for (int j = 0; j < J; ++j) store_item(j, M[j], L[j], o[j]);
+}
+
+template <int NT, int W, bool FIRST = false>
+__device__ __forceinline__ void merge_tile(const Params& p, float* lds, int64_t srow0, int64_t cstride, int s,
+                                           int64_t orow0, int tid, uint32_t first_rows = 0) {
+  constexpr int T = 64 * W;              // threads
+  constexpr int R = T / 32;              // rows that the threads' first float4 columns cover
+  constexpr int IPT = NT * 16 / R;       // float4 columns per thread where all NT x 16 rows are in use
+  constexpr int CB = da::kFusedBatch[NT - 1];
+  // Up to R rows need one column item per thread, which leaves registers for
+  // 16 chunks at once: B=1, H_KV=8, L_K=8192 in 16 chunks 12.0 -> 11.4 us per
+  // call against batches of 8.  Loads past the last chunk still take their
+  // turn and their code (4 chunks in a batch of 16: the step of 80 layers at
+  // L_K=512 515 -> 557 us; in a batch of 4, 507), so few chunks take a small
+  // batch, and more than 16, whose batches follow each other, the middle one.
+  if (p.hpt <= R && s <= 4)
+    merge_columns<W, 1, 4, FIRST>(p, lds, srow0, cstride, s, orow0, tid, first_rows);
+  else if (p.hpt <= R && (s <= 8 || s > 16))
+    merge_columns<W, 1, 8, FIRST>(p, lds, srow0, cstride, s, orow0, tid, first_rows);
+  else if (p.hpt <= R)
+    merge_columns<W, 1, 16, FIRST>(p, lds, srow0, cstride, s, orow0, tid, first_rows);
+  else if (IPT > 2 && p.hpt <= 2 * R)
+    merge_columns<W, 2, 8, FIRST>(p, lds, srow0, cstride, s, orow0, tid, first_rows);
+  else
+    merge_columns<W, IPT, CB, FIRST>(p, lds, srow0, cstride, s, orow0, tid, first_rows);
 }
 
 // One wave's running state over the 32-key tiles of a chunk: the packed query
@@ -636,16 +632,16 @@ constexpr int kSlotVals = 2 + 4 * NB;  // state values per lane and head tile: m
 template <int NT, int NB>
 __device__ __forceinline__ void publish_wave(const TileReducer<NT, NB>& red, float* slots, int wave, int lane) {
   constexpr int SV = kSlotVals<NB>;
-  float* v0 = slots + (size_t)wave * (NT * SV * 64) + lane;
+  float* v0 = slots + (size_t)wave * (NT * SV * 64);
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     float* v = v0 + nt * SV * 64;
-    v[0] = red.m[nt];
-    v[64] = sum_rows(red.l[nt]);
+    v[lane] = red.m[nt];
+    v[64 + lane] = sum_rows(red.l[nt]);
 #pragma unroll
     for (int nn = 0; nn < NB; ++nn)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) v[(2 + nn * 4 + i) * 64] = red.o[nt][nn][i];
+      for (int i = 0; i < 4; ++i) v[(2 + nn * 4 + i) * 64 + lane] = red.o[nt][nn][i];
   }
 }
 
@@ -1137,7 +1133,7 @@ split_partial_kernel(Params p) {
     // workgroup waits for another.  The last one sets the counter back to
     // zero for the next call.
     int s_m;
-    int64_t srow_m, cstride, nrows;
+    int64_t srow_m, cstride;
     uint32_t n;
     if constexpr (SCH) {
       // the sequence's chunks are state rows first, first + 1, ... (uniform across the workgroup)
@@ -1146,13 +1142,11 @@ split_partial_kernel(Params p) {
       n = (uint32_t)chunks;
       srow_m = (int64_t)first * p.H_Q + head0;
       cstride = p.H_Q;
-      nrows = (int64_t)p.state_rows * p.H_Q;
     } else {
       s_m = p.s;
       n = (uint32_t)p.s * VS;
       srow_m = row0_tile;
       cstride = rows;
-      nrows = (int64_t)p.s * rows;
     }
     __shared__ int s_last;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1167,7 +1161,7 @@ split_partial_kernel(Params p) {
     }
     __syncthreads();
     if (!s_last) return;
-    merge_tile<NT, W>(p, reinterpret_cast<float*>(smem), srow_m, cstride, s_m, row0_tile, nrows, tid);
+    merge_tile<NT, W>(p, reinterpret_cast<float*>(smem), srow_m, cstride, s_m, row0_tile, tid);
   }
 }
 
@@ -1554,8 +1548,8 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(1, 
     if (!s_last[k]) continue;  // uniform
     const Part part = k == 0 ? part_head : part_tail;
     merge_tile<NT, W, true>(p, reinterpret_cast<float*>(smem), (int64_t)2 * part.first * p.H_Q + head0,
-                            (int64_t)2 * p.H_Q, part.pieces, (int64_t)part.b * p.H_Q + head0,
-                            (int64_t)2 * p.groups * p.H_Q, tid, (uint32_t)p.H_Q);
+                            (int64_t)2 * p.H_Q, part.pieces, (int64_t)part.b * p.H_Q + head0, tid,
+                            (uint32_t)p.H_Q);
     __syncthreads();
   }
 }
