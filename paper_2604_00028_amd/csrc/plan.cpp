@@ -319,6 +319,21 @@ int kv_nontemporal(double key_rows, int readers) {
   return readers == 1 && key_rows * (2.0 * kHeadDim * 2.0) > (double)DA_RESIDENT_BYTES ? 1 : 0;
 }
 
+bool streams_kv(double key_rows, int readers) {
+  // K/V beyond half the MALL stay in it from call to call only in a program
+  // that reads nothing else in between, such as one layer called over and
+  // over; a decode step reads every other layer's first.  Measured both ways,
+  // hint off -> on.  Three batches in turn: schedules of 112-301 MB 1.05-1.19x
+  // faster (128 MQA sequences, 216 MB: 46.7 -> 40.4 us), fixed layouts of 201
+  // and 268 MB 37.5 -> 33.1 and 50.0 -> 40.9 us, dealt batches of 135, 202 and
+  // 268 MB 27.2 -> 23.1, 38.4 -> 33.3 and 49.2 -> 41.0 us.  One batch over and
+  // over: schedules 0.90-1.02x, fixed layouts 30.1 -> 33.1 and 39.5 -> 39.8 us,
+  // dealt batches 23.1 -> 22.2, 31.4 -> 32.5 and 41.2 -> 40.3 us.  Below the
+  // line what residency saves is the larger part (a schedule of 90 MB 0.98x
+  // even in turn; 16-64 MB called over and over up to 40%).
+  return readers == 1 && key_rows * (2.0 * kHeadDim * 2.0) > (double)(128ll << 20);
+}
+
 int check_shape(int B, int H_Q, int H_KV, int L_K_max, int d) {
   if (d != kHeadDim) return fail(DA_ERR_UNSUPPORTED, "head dim %d unsupported (only %d)", d, kHeadDim);
   if (B <= 0 || H_Q <= 0 || H_KV <= 0)
@@ -731,7 +746,8 @@ int make_schedule(const int32_t* seq_lens, int B, int H_Q, int H_KV, int L_K_max
   {
     double key_rows = 0.0;
     for (int b = 0; b < B; ++b) key_rows += (double)seq_lens[b] * H_KV;
-    out->kv_nontemporal = kv_nontemporal(key_rows, g / hpt);
+    // equal lengths keep the uniform plan's hint
+    out->kv_nontemporal = equal ? kv_nontemporal(key_rows, g / hpt) : streams_kv(key_rows, g / hpt) ? 1 : 0;
   }
   if (!meta) return fail(DA_ERR_NULL, "meta is NULL");
   if (meta_bytes < need)
@@ -801,13 +817,8 @@ bool dealt_plan(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int cus, De
   if (10 * groups * tps < 9 * cus) return false;  // CUs left over
   out->heads_per_tile = hpt;
   out->groups = groups;
-  // K/V beyond half the MALL are streamed: they share it with whatever else
-  // the program reads before the next call.  Measured over three batches in
-  // turn, 8 KV heads: 268 MB 49.2 -> 41.0 us with the hint, 202 MB 38.4 ->
-  // 33.3, 135 MB 27.2 -> 23.1, 103 MB 28.6 -> 27.6; the same batch over and
-  // over: 41.2 -> 40.3, 31.4 -> 32.5, 23.1 -> 22.2, but 24.3 -> 26.7 at 103 MB.
   const double most = (double)std::min<int64_t>(keys > 0 ? keys : INT64_MAX, (int64_t)B * L_K_max);
-  out->kv_nontemporal = g == hpt && most * H_KV * (2.0 * kHeadDim * 2.0) > (double)(128ll << 20) ? 1 : 0;
+  out->kv_nontemporal = streams_kv(most * H_KV, g / hpt) ? 1 : 0;
   return true;
 }
 
