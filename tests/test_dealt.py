@@ -58,7 +58,7 @@ def test_mixed_schedules_stream_beyond_half_the_mall():
     plan's line (288 MiB)."""
     at = (128 << 20) // (512 * 8)               # keys of 8 KV heads in 128 MiB
     for keys, want in ((at - 4096, 0), (at + 4096, 1)):
-        lens = [keys - 10 * 3000 - 7] + [3000] * 10
+        lens = [keys - 10 * 2000 - 7] + [2000] * 10
         sched, _ = da.da_make_schedule(lens, 64, 8, num_cus=256)
         assert sched.kv_nontemporal == want
     equal, _ = da.da_make_schedule([at // 8 + 32] * 8, 64, 8, num_cus=256)
