@@ -64,3 +64,19 @@ def test_mixed_schedules_stream_beyond_half_the_mall():
     equal, _ = da.da_make_schedule([at // 8 + 32] * 8, 64, 8, num_cus=256)
     shared, _ = da.da_make_schedule([at * 2, 3000], 128, 2, num_cus=256)      # two head tiles read each key
     assert equal.kv_nontemporal == 0 and shared.kv_nontemporal == 0
+
+
+def test_long_mixed_schedules_are_dealt():
+    """Chosen schedules of mixed lengths with 128 tiles and more a share are
+    marked; equal lengths, a forced chunk length, wide groups and short shares
+    keep their chunks.  The workspace holds either launch."""
+    mixed = [1024 + 480 * i for i in range(32)]
+    sched, _ = da.da_make_schedule(mixed, 64, 8, num_cus=256)
+    assert sched.kv_fetch & 4 and sched.kv_fetch & 3 in (0, 1, 2) and sched.combine == 1
+    chunks = sched.state_rows * 64 * (128 + 2) * 4 + (1 << 20)
+    assert da.da_schedule_workspace_bytes(sched) >= max(chunks, da.da_dealt_workspace_bytes(32, 64, 8, 256))
+    for lens, H_Q, H_KV, kw in ((mixed, 64, 8, dict(chunk_tiles=60)), (mixed, 64, 8, dict(pack_gqa=0)),
+                                ([8192] * 31, 64, 8, {}), (mixed, 64, 2, {}), ([x // 8 for x in mixed], 64, 8, {}),
+                                ([20000] * 2 + [600] * 400, 64, 8, {})):
+        s, _ = da.da_make_schedule(lens, H_Q, H_KV, num_cus=256, **kw)
+        assert s.kv_fetch <= 2, (H_Q, H_KV, kw)
