@@ -30,6 +30,8 @@ the host cores (a reported baseline only).  Compact summaries come last.
 from __future__ import annotations
 
 import argparse
+import contextlib
+import gc
 import hashlib
 import json
 import os
@@ -119,6 +121,18 @@ def parse():
     return ap.parse_args()
 
 
+@contextlib.contextmanager
+def no_gc():
+    """No cyclic garbage collection inside: one that frees an older variant's
+    graph during a capture ends the process."""
+    gc.collect()
+    gc.disable()
+    try:
+        yield
+    finally:
+        gc.enable()
+
+
 class Variant:
     """K calls of one launch configuration captured in a HIP graph."""
 
@@ -153,7 +167,7 @@ class Variant:
             call(i)
         torch.cuda.synchronize()
         self.graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(self.graph):
+        with no_gc(), torch.cuda.graph(self.graph):
             for i in range(steps):
                 call(i)
         self.graph.replay()
@@ -200,7 +214,7 @@ class Timed:
             call(i)
         torch.cuda.synchronize()
         self.graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(self.graph):
+        with no_gc(), torch.cuda.graph(self.graph):
             for i in range(steps):
                 call(i)
         self.graph.replay()
