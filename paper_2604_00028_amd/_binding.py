@@ -11,7 +11,7 @@ from __future__ import annotations
 
 import ctypes
 import os
-from typing import Callable, Dict, List, Optional, Sequence, Tuple
+from typing import Dict, List, Optional, Sequence, Tuple
 
 import torch
 
@@ -318,19 +318,16 @@ def workspace_for(dev: torch.device, stream_handle: int, nbytes: int) -> torch.T
     return ws
 
 
-def _planned_inside(call, dev: torch.device, s_handle: int, workspace: Optional[torch.Tensor],
-                    need: Callable[[], int]) -> None:
-    """Run an entry point that plans for itself: call(workspace pointer,
-    bytes) returns its status.  Without a workspace of the caller's, the one
-    cached for this stream is offered as it is; only where the plan needs a
-    larger one (which the entry point finds before it launches anything) is the
-    plan made here too, for need()'s bytes."""
-    ws = workspace if workspace is not None else _workspaces.get((dev.index, s_handle))
-    rc = call(_ptr(ws), ws.numel() * ws.element_size() if ws is not None else 0)
-    if rc == DA_ERR_WORKSPACE and workspace is None:
-        ws = workspace_for(dev, s_handle, need())
-        rc = call(_ptr(ws), ws.numel() * ws.element_size())
-    _check(rc)
+def _offered(workspace: Optional[torch.Tensor], dev: torch.device, s_handle: int) -> Optional[torch.Tensor]:
+    """The workspace to offer an entry point that plans for itself: the
+    caller's, or the one cached for this stream as it is.  Only where the plan
+    needs a larger one, which the entry point finds before it launches
+    anything, is the plan made here too and the cached one grown."""
+    return workspace if workspace is not None else _workspaces.get((dev.index, s_handle))
+
+
+def _nbytes(t: Optional[torch.Tensor]) -> int:
+    return t.numel() * t.element_size() if t is not None else 0
 
 
 def da_decode_attn(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, cu_seqlens_k: Optional[torch.Tensor] = None,
@@ -348,12 +345,16 @@ def da_decode_attn(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, cu_seqlens
     if out is None:
         out = _new_out(q)
     s_handle = _stream(dev, stream)
-    _planned_inside(
-        lambda ws, n: load().da_decode_attn(_ptr(q), _ptr(k), _ptr(v), _ptr(cu_seqlens_k), _ptr(out), _ptr(lse_out),
-                                            B, H_Q, H_KV, L, d, float(softmax_scale), int(num_splits), int(pack_gqa),
-                                            ws, n, s_handle),
-        dev, s_handle, workspace,
-        lambda: da_workspace_bytes(B, H_Q, d, da_make_plan(B, H_Q, H_KV, L, d, num_splits, pack_gqa).num_splits))
+    ws = _offered(workspace, dev, s_handle)
+    while True:
+        rc = load().da_decode_attn(_ptr(q), _ptr(k), _ptr(v), _ptr(cu_seqlens_k), _ptr(out), _ptr(lse_out),
+                                   B, H_Q, H_KV, L, d, float(softmax_scale), int(num_splits), int(pack_gqa),
+                                   _ptr(ws), _nbytes(ws), s_handle)
+        if rc != DA_ERR_WORKSPACE or workspace is not None:
+            break
+        plan = da_make_plan(B, H_Q, H_KV, L, d, num_splits, pack_gqa)
+        workspace = ws = workspace_for(dev, s_handle, da_workspace_bytes(B, H_Q, d, plan.num_splits))
+    _check(rc)
     return out
 
 
@@ -431,13 +432,17 @@ def da_decode_attn_paged(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.
         out = _new_out(q)
     s_handle = _stream(dev, stream)
     L = int(L_K_max)
-    _planned_inside(
-        lambda ws, n: load().da_decode_attn_paged(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table),
-                                                  _ptr(seq_lens), _ptr(out), _ptr(lse_out), B, H_Q, H_KV, page_size,
-                                                  max_pages, num_pages, L, d, float(softmax_scale), int(num_splits),
-                                                  int(pack_gqa), ws, n, s_handle),
-        dev, s_handle, workspace,
-        lambda: da_workspace_bytes(B, H_Q, d, da_make_plan(B, H_Q, H_KV, L, d, num_splits, pack_gqa).num_splits))
+    ws = _offered(workspace, dev, s_handle)
+    while True:
+        rc = load().da_decode_attn_paged(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table), _ptr(seq_lens),
+                                         _ptr(out), _ptr(lse_out), B, H_Q, H_KV, page_size, max_pages, num_pages, L,
+                                         d, float(softmax_scale), int(num_splits), int(pack_gqa), _ptr(ws),
+                                         _nbytes(ws), s_handle)
+        if rc != DA_ERR_WORKSPACE or workspace is not None:
+            break
+        plan = da_make_plan(B, H_Q, H_KV, L, d, num_splits, pack_gqa)
+        workspace = ws = workspace_for(dev, s_handle, da_workspace_bytes(B, H_Q, d, plan.num_splits))
+    _check(rc)
     return out
 
 

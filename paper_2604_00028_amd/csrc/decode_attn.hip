@@ -41,6 +41,9 @@
 //  * K/V loads are raw buffer loads whose record count ends at the wave's
 //    last key: keys past it read as zeros without touching memory, so ragged
 //    tails cost no traffic and no load needs a mask or a branch.
+//  * Batches of mixed lengths whose keys fill the chip take the dealt launch
+//    instead (dealt_kernel): the batch's tiles are shared evenly among the
+//    CUs, across sequence ends.
 //  * With packing off, workgroup ids are remapped so consecutive tiles land
 //    on the same XCD (dispatch is round-robin over the 8 XCDs): the query
 //    heads of one KV head then share that XCD's L2.  With packing on, each
@@ -438,6 +441,7 @@ __device__ __forceinline__ void merge_columns(const Params& p, float* lds, int64
   for (int j = 0; j < J; ++j) store_item(j, M[j], L[j], o[j]);
 }
 
+// merge_columns by the rows and chunks in use.
 template <int NT, int W, bool FIRST = false>
 __device__ __forceinline__ void merge_tile(const Params& p, float* lds, int64_t srow0, int64_t cstride, int s,
                                            int64_t orow0, int tid, uint32_t first_rows = 0) {
@@ -499,6 +503,12 @@ struct TileReducer {
 #pragma unroll
       for (int nn = 0; nn < NB; ++nn) o[nt][nn] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
+  }
+
+  // l summed over the row groups, once the last tile is in.
+  __device__ __forceinline__ void close() {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) l[nt] = sum_rows(l[nt]);
   }
 
   // S^T[16 keys x 16 heads] per (mt, nt) from the tile's 8 K operands.
@@ -620,7 +630,7 @@ struct TileReducer {
 };
 
 // A chunk's W wave states are merged in one step.  Every wave publishes its
-// state (per head column: running max, row-summed l, NB x 4 output values;
+// closed state (per head column: running max, row-summed l, NB x 4 output values;
 // all waves share one lane layout) to its LDS slot, value-major
 // ([value][lane], conflict-free).  After a barrier (the caller's), wave w
 // merges the W states for its NB/W blocks of 16 output dims -- maximum,
@@ -637,7 +647,7 @@ __device__ __forceinline__ void publish_wave(const TileReducer<NT, NB>& red, flo
   for (int nt = 0; nt < NT; ++nt) {
     float* v = v0 + nt * SV * 64;
     v[lane] = red.m[nt];
-    v[64 + lane] = sum_rows(red.l[nt]);
+    v[64 + lane] = red.l[nt];
 #pragma unroll
     for (int nn = 0; nn < NB; ++nn)
 #pragma unroll
@@ -1112,6 +1122,7 @@ split_partial_kernel(Params p) {
   const bool direct = SCH ? prow < 0 : p.mode == kDirect;
   // first chunk-state row of this workgroup's heads
   const int64_t srow0 = direct ? 0 : (SCH ? (int64_t)prow * p.H_Q + head0 : (int64_t)split * rows + row0_tile);
+  red.close();
   __syncthreads();  // every wave is done with its stages
   publish_wave(red, reinterpret_cast<float*>(smem), wave, lane);
   __syncthreads();
@@ -1212,7 +1223,8 @@ constexpr int dealt_smem_bytes(int W, int NT) {
 // Whole sequences are written at once; of the two it shares with its
 // neighbours, each workgroup writes the chunk states, and the last workgroup
 // to arrive at a sequence's head tile merges them (the hand-off of
-// split_partial_kernel).
+// split_partial_kernel; every wave takes its own ticket).  Nobody waits for
+// another workgroup.
 //
 // Every wave finds the deal for itself from the lengths (one load per 64
 // sequences, scanned across the lanes; 0.7-1.0 us).  K and V take the
@@ -1230,8 +1242,8 @@ constexpr int dealt_smem_bytes(int W, int NT) {
 // GB) 234 -> 164 us against one split for all (6.4 TB/s; workgroups end
 // within 8% of each other, which is what is lost against equal lengths: 32 of
 // 8192 keys take 150.5 us, 7.1 TB/s), 64 sequences of 140 to 22365 keys over
-// 4 KV heads in 64-key pages (0.5 GB) 258 -> 88 us.  Four waves measured 4%
-// slower on both; two workgroups a CU 3-6%.  The fixed part is about 8 us, of
+// 4 KV heads in 64-key pages (0.5 GB) 258 -> 88 us.  Four waves measured
+// 1-4% slower, three 1-4%, two workgroups a CU 1-9%.  The fixed part is about 8 us, of
 // it 2-4 for the merge, so short batches stay with one split count
 // (prefers_dealt), and no workgroup takes fewer tiles than about the square
 // root of the longest sequence's: fewer, longer pieces, whose merge is
@@ -1530,6 +1542,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(1, 
       else
         part_tail = part;
     }
+    red.close();
     lds_barrier();  // the last segment's slots have been read
     publish_wave(red, slots, wave, lane);
     lds_barrier();

@@ -74,8 +74,10 @@ double model_time(const CostModel& m, int B, int H_Q, int H_KV, int L_K, int hpt
                   bool fused = false, double beat = INFINITY);
 
 // Chunk states the merging workgroup of a single-launch merge loads at once
-// (16-column / 32-column head tiles): one batch is merged in registers, more
-// are staged through LDS batch by batch.
+// (16-column / 32-column head tiles), as the cost model prices it: one batch
+// is merged in registers, more are staged through LDS batch by batch.  Tiles of
+// at most 8 heads take up to 16 at once (merge_tile), which the fitted
+// constants do not know.
 constexpr int kFusedBatch[2] = {8, 4};
 
 // Modelled time (us) the merge of s chunk states of tiles of `hpt` heads adds
