@@ -1149,6 +1149,8 @@ split_partial_kernel(Params p) {
     if constexpr (SCH) {
       // the sequence's chunks are state rows first, first + 1, ... (uniform across the workgroup)
       const int first = p.seqs[2 * b], chunks = p.seqs[2 * b + 1];
+      // not a schedule of this shape: rows outside the workspace would be merged
+      if (first < 0 || chunks < 2 || chunks > DA_MAX_SPLITS || first > p.state_rows - chunks) return;
       s_m = chunks;
       n = (uint32_t)chunks;
       srow_m = (int64_t)first * p.H_Q + head0;

@@ -375,3 +375,36 @@ def test_scheduled_merge_graph_replay(comb):
         again = da.da_decode_attn_scheduled(q, k, v, sched, meta_dev, cu_seqlens_k=cu)
         torch.cuda.synchronize()
         assert torch.equal(again.view(torch.int16), eager.view(torch.int16))
+
+
+# A sequence table entry {first state row, chunk count} that does not fit a schedule of R state rows.
+FOREIGN_ROWS = [lambda R: (-1, 4), lambda R: (R, 4), lambda R: (R - 3, 4), lambda R: (2**31 - 1, 4), lambda R: (0, 65),
+                lambda R: (0, 2**31 - 1), lambda R: (0, 1), lambda R: (0, -7)]
+
+
+@pytest.mark.parametrize("comb", [1])
+@pytest.mark.parametrize("entry", range(len(FOREIGN_ROWS)))
+def test_rows_outside_the_workspace_are_not_merged(comb, entry):
+    """Metadata whose sequence table names state rows the schedule does not
+    have: that sequence is left unwritten, the others are right, and the
+    arrival counters end at zero."""
+    H_Q, H_KV, lens = 16, 2, [700, 900, 33]
+    inp = make_inputs(custom_shape(3, H_Q, H_KV, 900, varlen=True), seed=5, lengths=lens)
+    O, lse = decode_attention(inp.q, inp.k, inp.v, inp.lengths, inp.cu_seqlens_k)
+    q, k, v, cu = dev_inputs(inp)
+    sched, meta = da.da_make_schedule(lens, H_Q, H_KV, 900, chunk_tiles=6)
+    assert sched.state_rows > 4
+    sched.combine = comb
+    table = meta[sched.seq_offset:].view(torch.int32).view(3, 2)
+    table[1] = torch.tensor(FOREIGN_ROWS[entry](sched.state_rows), dtype=torch.int32)
+    say(f"foreign rows {table[1].tolist()} of {sched.state_rows} combine={comb}")
+    ws = torch.zeros(da.da_schedule_workspace_bytes(sched), dtype=torch.uint8, device="cuda")
+    out = torch.full((3, H_Q, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lse_t = torch.empty(3, H_Q, dtype=torch.float32, device="cuda")
+    da.da_decode_attn_scheduled(q, k, v, sched, meta.cuda(), cu_seqlens_k=cu, out=out, lse_out=lse_t, workspace=ws)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(out[1].float()).all())
+    assert int(ws[-(1 << 20):].max()) == 0
+    keep = [0, 2]
+    assert_parity(out[keep], O[keep], "sequences beside foreign rows")
+    check_lse(lse_t[keep], lse[keep])
