@@ -1582,8 +1582,8 @@ __global__ void __launch_bounds__(256) split_combine_kernel(const float* __restr
                                                             const float* __restrict__ l_part,
                                                             uint16_t* __restrict__ out, float* __restrict__ lse,
                                                             int s, int64_t rows,
-                                                            const int32_t* __restrict__ seqs, int H_Q,
-                                                            Div div_hq) {
+                                                            const int32_t* __restrict__ seqs, int state_rows,
+                                                            int H_Q, Div div_hq) {
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
   const int64_t row = (int64_t)blockIdx.x * 4 + w;
@@ -1597,8 +1597,8 @@ __global__ void __launch_bounds__(256) split_combine_kernel(const float* __restr
     const int h = (int)row - b * H_Q;
     const int r0 = seqs[2 * b];
     s = seqs[2 * b + 1];
-    if (r0 < 0 || s <= 1) return;
-    s = s < DA_MAX_SPLITS ? s : DA_MAX_SPLITS;
+    // not split, or not a schedule of this shape
+    if (r0 < 0 || s < 2 || s > DA_MAX_SPLITS || r0 > state_rows - s) return;
     base = (int64_t)r0 * H_Q + h;
     srow = H_Q;
   }
@@ -1750,10 +1750,11 @@ int launch_partial(const Params& prm, const da_plan& pl, hipStream_t stream) {
 }
 
 int launch_combine(const float* o_part, const float* m_part, const float* l_part, uint16_t* out, float* lse,
-                   int s, int64_t rows, hipStream_t stream, const int32_t* seqs = nullptr, int H_Q = 1) {
+                   int s, int64_t rows, hipStream_t stream, const int32_t* seqs = nullptr, int state_rows = 0,
+                   int H_Q = 1) {
   const int grid = (int)((rows + 3) / 4);
   Div div_hq = make_div((uint32_t)H_Q);
-  void* args[] = {&o_part, &m_part, &l_part, &out, &lse, &s, &rows, &seqs, &H_Q, &div_hq};
+  void* args[] = {&o_part, &m_part, &l_part, &out, &lse, &s, &rows, &seqs, &state_rows, &H_Q, &div_hq};
   const void* fn = seqs ? reinterpret_cast<const void*>(&split_combine_kernel<true>)
                         : reinterpret_cast<const void*>(&split_combine_kernel<false>);
   hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(256), args, 0, stream);
@@ -2241,7 +2242,7 @@ int da_decode_attn_scheduled(const void* q, const void* k, const void* v, const 
   rc = launch_partial(p, pl, static_cast<hipStream_t>(stream));
   if (rc || !need || sched->combine) return rc;
   return launch_combine(p.o_part, p.m_part, p.l_part, static_cast<uint16_t*>(out), lse_out, sched->max_splits,
-                        (int64_t)B * H_Q, static_cast<hipStream_t>(stream), seqs, H_Q);
+                        (int64_t)B * H_Q, static_cast<hipStream_t>(stream), seqs, sched->state_rows, H_Q);
 }
 
 int da_decode_attn_dealt(const void* q, const void* k, const void* v, const int32_t* cu_seqlens_k,

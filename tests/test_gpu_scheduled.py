@@ -382,7 +382,7 @@ FOREIGN_ROWS = [lambda R: (-1, 4), lambda R: (R, 4), lambda R: (R - 3, 4), lambd
                 lambda R: (0, 2**31 - 1), lambda R: (0, 1), lambda R: (0, -7)]
 
 
-@pytest.mark.parametrize("comb", [1])
+@pytest.mark.parametrize("comb", [1, 0])
 @pytest.mark.parametrize("entry", range(len(FOREIGN_ROWS)))
 def test_rows_outside_the_workspace_are_not_merged(comb, entry):
     """Metadata whose sequence table names state rows the schedule does not
