@@ -529,8 +529,11 @@ struct TileReducer {
   // max is taken on raw scores (the scale is positive) and each exponent is
   // one fma, raw * scale*log2(e) - running max.  `last`: only the final tile
   // can be shorter than 32 keys and needs its scores masked.
-  template <typename Last>
-  __device__ __forceinline__ void softmax(const f32x4 (&sc)[NT][2], int nvalid, Last last, bf16x8 (&pb)[NT]) {
+  // PARTS 2 keeps what rounding the probabilities to bf16 leaves over as a
+  // second operand (pb[1]; the difference is exact in fp32).
+  template <int PARTS, typename Last>
+  __device__ __forceinline__ void softmax(const f32x4 (&sc)[NT][2], int nvalid, Last last,
+                                          bf16x8 (&pb)[PARTS][NT]) {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       float x[8];
@@ -565,7 +568,17 @@ struct TileReducer {
       pk.y = pack_bf16x2(x[2], x[3]);
       pk.z = pack_bf16x2(x[4], x[5]);
       pk.w = pack_bf16x2(x[6], x[7]);
-      pb[nt] = as_bf16x8(pk);
+      pb[0][nt] = as_bf16x8(pk);
+      if constexpr (PARTS == 2) {
+        auto low = [&](uint32_t two, int e) {  // bf16 pair `two` stands for x[e], x[e + 1]
+          return pack_bf16x2(x[e] - __uint_as_float(two << 16), x[e + 1] - __uint_as_float(two & 0xffff0000u));
+        };
+        pk.x = low(pk.x, 0);
+        pk.y = low(pk.y, 2);
+        pk.z = low(pk.z, 4);
+        pk.w = low(pk.w, 6);
+        pb[1][nt] = as_bf16x8(pk);
+      }
     }
   }
 
@@ -584,8 +597,8 @@ struct TileReducer {
   // offsets), the reads are written as inline assembly followed by an
   // explicit wait: the compiler cannot tell that they touch the other stage
   // and would otherwise drain every outstanding load before them.
-  template <typename Addr, typename Opaque>
-  __device__ __forceinline__ void pv(const bf16x8 (&pb)[NT], Addr vaddr, Opaque opaque) {
+  template <int PARTS, typename Addr, typename Opaque>
+  __device__ __forceinline__ void pv(const bf16x8 (&pb)[PARTS][NT], Addr vaddr, Opaque opaque) {
     s16x4 vlo[NB], vhi[NB];
     if constexpr (Opaque::value) {
 #pragma unroll
@@ -618,13 +631,15 @@ struct TileReducer {
       }
     }
     __builtin_amdgcn_sched_group_barrier(0x100, 2 * NB, 0);   // the DS reads first
-    __builtin_amdgcn_sched_group_barrier(0x008, NB * NT, 0);  // then the MFMAs
+    __builtin_amdgcn_sched_group_barrier(0x008, PARTS * NB * NT, 0);  // then the MFMAs
 #pragma unroll
     for (int nn = 0; nn < NB; ++nn) {
       const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(vlo[nn], vhi[nn], 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-        o[nt][nn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pb[nt], o[nt][nn], 0, 0, 0);
+      for (int i = PARTS - 1; i >= 0; --i)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+          o[nt][nn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pb[i][nt], o[nt][nn], 0, 0, 0);
     }
   }
 };
@@ -998,7 +1013,7 @@ split_partial_kernel(Params p) {
 
       if constexpr (decltype(prefetch)::value) load_tile(kreg, vreg, t + 1);
 
-      bf16x8 pb[NT];
+      bf16x8 pb[1][NT];
       red.softmax(sc, nvalid, last, pb);
       __builtin_amdgcn_wave_barrier();
       const unsigned char* vrow = vstage + (quad * 4 + (col >> 2)) * kVPitch + 8 * (col & 3);
@@ -1082,7 +1097,7 @@ split_partial_kernel(Params p) {
               (uintptr_t)(kro[mt][j] + so)));
       f32x4 sc[NT][2];
       red.scores(kop, sc);
-      bf16x8 pb[NT];
+      bf16x8 pb[1][NT];
       red.softmax(sc, key_hi - (key_lo + t * kstep), last, pb);
       red.pv(pb, [&](int mt, int nn) { return vro[mt][nn] + so; }, yes);
     };
@@ -1239,6 +1254,14 @@ constexpr int dealt_smem_bytes(int W, int NT) {
 // streams.  The ticket of a workgroup's first shared chunk is taken two tiles
 // into the next sequence, when its stores are complete anyway, so that one
 // merge, not two, is left at the end.
+//
+// The probabilities enter the second product in two bf16 parts.  The largest
+// probability of a piece is exactly 1, so fewer and longer pieces leave more
+// of them to rounding: in one part the relative error against 64 bits was
+// 1.84-2.14e-3 where 16 splits of the same batch have 1.72-2.10e-3, in two it
+// is 1.64-1.68e-3 (rounding the output alone gives 1.66e-3).  The matrix cores
+// have the time: 160.8 and 160.9 us on the packed batch below, 86.4 and 86.9
+// on the paged one.
 //
 // Bound by HBM: 32 sequences of 1024 to 16384 keys over 8 KV heads (1.06
 // GB) 234 -> 164 us against one split for all (6.4 TB/s; workgroups end
@@ -1524,7 +1547,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(1, 
 #pragma unroll
             for (int e = 0; e < 4; ++e) sc[nt][mt][e] = mt * 16 + quad * 4 + e < nvalid ? sc[nt][mt][e] : -INFINITY;
       }
-      bf16x8 pb[NT];
+      bf16x8 pb[2][NT];
       red.softmax(sc, kKeysPerTile, no, pb);
       __builtin_amdgcn_wave_barrier();
       const unsigned char* vrow = vstage + (quad * 4 + (col >> 2)) * kVPitch + 8 * (col & 3);

@@ -11,7 +11,7 @@ import torch
 import paper_2604_00028_amd as da
 from oracle import decode_attention
 from workloads import custom_shape, make_inputs, paged_layout
-from tests.gpu_helpers import assert_parity, dev_inputs, say, to_dev
+from tests.gpu_helpers import assert_parity, dev_inputs, say, to_dev, to_f64
 
 pytestmark = pytest.mark.gpu
 
@@ -148,3 +148,35 @@ def test_dealt_schedule(layout):
             if mark and combine and layout != "fixed":
                 same = da.da_decode_attn_dealt(q, k, v, 1500, **kw)
                 assert torch.equal(out.view(torch.int16), same.view(torch.int16))
+
+
+@pytest.mark.parametrize("page", [None, 64])
+@pytest.mark.parametrize("H_Q,H_KV,lengths,scale", [
+    (64, 8, [8192, 3000, 6001], 2.0), (8, 1, [20000, 700], 2.0), (16, 2, [5000] * 6, 1.0), (32, 1, [4100, 9000], 1.0)])
+def test_dealt_is_no_further_from_64_bits(H_Q, H_KV, lengths, scale, page):
+    """The deal cuts a batch into fewer and longer pieces than a launch with
+    many splits.  A piece's largest probability is exactly 1, so fewer pieces
+    leave more probabilities to rounding; the dealt launch carries their
+    remainders, and its error is no larger than that of 16 splits (whose own
+    probabilities are rounded to bf16 once)."""
+    B, L = len(lengths), max(lengths)
+    inp = make_inputs(custom_shape(B, H_Q, H_KV, L, varlen=True), seed=23, lengths=lengths)
+    q, k, v, cu = dev_inputs(inp)
+    q = q * scale                        # exact: a power of two
+    qh = (inp.q if scale == 1.0 else q.cpu().view(torch.int16).numpy().view(np.uint16))
+    O, _ = decode_attention(qh, inp.k, inp.v, inp.lengths, inp.cu_seqlens_k)
+    kw, ukw = dict(cu_seqlens_k=cu), dict(cu_seqlens_k=cu, L_K_max=L)
+    if page is not None:
+        pg = paged_layout(inp, page, seed=2)
+        k, v = to_dev(pg.k_cache), to_dev(pg.v_cache)
+        kw = dict(block_table=torch.from_numpy(pg.block_table).cuda(), seq_lens=torch.from_numpy(pg.seq_lens).cuda())
+    say(f"dealt error {H_Q}/{H_KV} {lengths} page={page}")
+    dealt = da.da_decode_attn_dealt(q, k, v, L, **kw)
+    if page is None:
+        split = da.da_decode_attn(q, k, v, num_splits=16, **ukw)
+    else:
+        split = da.da_decode_attn_paged(q, k, v, kw["block_table"], kw["seq_lens"], L, num_splits=16)
+    torch.cuda.synchronize()
+    rel = [float(np.linalg.norm(to_f64(x) - O) / np.linalg.norm(O)) for x in (dealt, split)]
+    say(f"  dealt {rel[0]:.3e} 16 splits {rel[1]:.3e}")
+    assert rel[0] <= rel[1]
