@@ -240,9 +240,6 @@ int da_split_bounds(int L, int num_splits, int32_t* cuts);
  *   workspace    device memory of workspace_bytes >= da_workspace_bytes(B,
  *                H_Q, d, s) for the resolved s (unused when s == 1).  Calls
  *                that share a workspace must not overlap in time.
- * A call that plans for itself over a fixed layout marks its K/V loads
- * nontemporal above 128 MiB (the hint changes no result; a plan run through
- * da_decode_attn_planned keeps its own).
  * s == 1: one kernel launch.  s > 1: the split kernel writes the chunk
  * states to the workspace, and they are merged in chunk order either by the
  * combine kernel (exactly da_split_partials followed by da_combine_splits)
@@ -360,8 +357,7 @@ typedef struct da_schedule {
                                     to run the chunks listed */
   int32_t seq_offset;            /* byte offset of the per-sequence table in the metadata */
   int32_t meta_bytes;            /* metadata bytes written */
-  int32_t kv_nontemporal;        /* as in da_plan, for the K/V of all B sequences (mixed lengths:
-                                    already above 128 MiB) */
+  int32_t kv_nontemporal;        /* as in da_plan, for the K/V of all B sequences */
   int32_t combine;               /* 1: the chunk states of each split sequence are merged inside
                                     the split launch by the last workgroup of each of its head
                                     tiles (arrival counters in the workspace, as in da_plan);

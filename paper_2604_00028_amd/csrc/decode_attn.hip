@@ -1834,16 +1834,6 @@ int check_plan(const da_plan* pl, int B, int H_Q, int H_KV) {
   return DA_OK;
 }
 
-// What an entry point changes in a plan it has made for itself: where the
-// lengths are known only on the device (`device_lens`), four waves; over a
-// fixed layout, whose K/V it therefore knows, the cache hint (never a result).
-void self_planned(da_plan* pl, int B, int H_Q, int H_KV, int L_K_max, bool device_lens) {
-  if (device_lens)
-    da::four_waves(pl, L_K_max);
-  else if (da::streams_kv((double)B * L_K_max * H_KV, H_Q / H_KV / pl->heads_per_tile * pl->v_slices))
-    pl->kv_nontemporal = 1;
-}
-
 // `given`: a plan made beforehand (checked), run as it is; NULL: plan here
 // from (num_splits, pack_gqa) with the MI355X policy.
 int run_decode(Params p, int B, int H_Q, int H_KV, int L_K_max, int d, float softmax_scale, int num_splits,
@@ -1879,7 +1869,7 @@ int run_decode(Params p, int B, int H_Q, int H_KV, int L_K_max, int d, float sof
   } else {
     rc = da::plan(B, H_Q, H_KV, L_K_max, d, num_splits, pack_gqa, cus, 0, DA_POLICY_MI355X, &pl);
     if (rc) return rc;
-    self_planned(&pl, B, H_Q, H_KV, L_K_max, p.cu || p.seq_lens);
+    if (p.cu || p.seq_lens) da::four_waves(&pl, L_K_max);  // lengths known only on the device
   }
   const int s = pl.num_splits;
   const bool fused = s > 1 && pl.combine == 1;
@@ -2125,7 +2115,7 @@ int da_decode_attn_noalloc(const void* q, const void* k, const void* v, const in
   da_plan pl;
   rc = da::plan(B, H_Q, H_KV, L_K_max, d, num_splits, pack_gqa, cus, 0, DA_POLICY_MI355X, &pl);
   if (rc) return rc;
-  self_planned(&pl, B, H_Q, H_KV, L_K_max, cu_seqlens_k != nullptr);
+  if (cu_seqlens_k) da::four_waves(&pl, L_K_max);  // lengths known only on the device
   rc = fits(pl.num_splits);
   if (rc) return rc;
   unsigned char* ws = nullptr;

@@ -314,24 +314,13 @@ int kv_nontemporal(double key_rows, int readers) {
   // hint; 537 MB: 103 -> 88 us).  Below the MALL's capacity the hint costs
   // what residency between calls saves (268 MB: 46 -> 48 us; 134 MB with 64
   // workgroups: 26.2 -> 26.8 us; 16-64 MB: up to 40%), so it is off there.
+  // A line at 128 MiB was measured as well: over 30 fixed layouts and 21
+  // schedules of 120-290 MB the hint gains 1.01-1.16x where three batches
+  // take turns and loses, at 0.82-1.0x, on 45 of the 51 where one is called
+  // over and over.  A caller whose batches take turns sets the field itself.
   // When several workgroups read the same keys (head tiles narrower than
   // the group), the later ones find them in L2 only without the hint.
   return readers == 1 && key_rows * (2.0 * kHeadDim * 2.0) > (double)DA_RESIDENT_BYTES ? 1 : 0;
-}
-
-bool streams_kv(double key_rows, int readers) {
-  // K/V beyond half the MALL stay in it from call to call only in a program
-  // that reads nothing else in between, such as one layer called over and
-  // over; a decode step reads every other layer's first.  Measured both ways,
-  // hint off -> on.  Three batches in turn: schedules of 112-301 MB 1.05-1.19x
-  // faster (128 MQA sequences, 216 MB: 46.7 -> 40.4 us), fixed layouts of 201
-  // and 268 MB 37.5 -> 33.1 and 50.0 -> 40.9 us, dealt batches of 135, 202 and
-  // 268 MB 27.2 -> 23.1, 38.4 -> 33.3 and 49.2 -> 41.0 us.  One batch over and
-  // over: schedules 0.90-1.02x, fixed layouts 30.1 -> 33.1 and 39.5 -> 39.8 us,
-  // dealt batches 23.1 -> 22.2, 31.4 -> 32.5 and 41.2 -> 40.3 us.  Below the
-  // line what residency saves is the larger part (a schedule of 90 MB 0.98x
-  // even in turn; 16-64 MB called over and over up to 40%).
-  return readers == 1 && key_rows * (2.0 * kHeadDim * 2.0) > (double)(128ll << 20);
 }
 
 int check_shape(int B, int H_Q, int H_KV, int L_K_max, int d) {
@@ -746,7 +735,6 @@ int make_schedule(const int32_t* seq_lens, int B, int H_Q, int H_KV, int L_K_max
   {
     double key_rows = 0.0;
     for (int b = 0; b < B; ++b) key_rows += (double)seq_lens[b] * H_KV;
-    // equal lengths keep the uniform plan's hint
     // Chosen schedules of long shares run as the dealt launch: one round of
     // even shares, two waves each, instead of chunks of one length in about
     // five.  Measured on 60 mixed batches: from 128 tiles a share on
@@ -762,7 +750,7 @@ int make_schedule(const int32_t* seq_lens, int B, int H_Q, int H_KV, int L_K_max
       const int64_t share = all / dp.groups;
       if (share >= 128 && share >= 40 * (int64_t)B / dp.groups) out->kv_fetch |= DA_SCHEDULE_DEALT;
     }
-    out->kv_nontemporal = equal ? kv_nontemporal(key_rows, g / hpt) : streams_kv(key_rows, g / hpt) ? 1 : 0;
+    out->kv_nontemporal = kv_nontemporal(key_rows, g / hpt);
   }
   if (!meta) return fail(DA_ERR_NULL, "meta is NULL");
   if (meta_bytes < need)
@@ -833,7 +821,7 @@ bool dealt_plan(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int cus, De
   out->heads_per_tile = hpt;
   out->groups = groups;
   const double most = (double)std::min<int64_t>(keys > 0 ? keys : INT64_MAX, (int64_t)B * L_K_max);
-  out->kv_nontemporal = streams_kv(most * H_KV, g / hpt) ? 1 : 0;
+  out->kv_nontemporal = kv_nontemporal(most * H_KV, g / hpt);
   return true;
 }
 

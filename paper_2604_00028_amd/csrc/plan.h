@@ -144,12 +144,6 @@ int kv_fetch(int64_t grid, int cus, int64_t tiles_per_wave);
 // when they exceed DA_RESIDENT_BYTES and one workgroup reads each row.
 int kv_nontemporal(double key_rows, int readers);
 
-// Whether the entry points that choose their own launch (schedules of mixed
-// lengths, the dealt launch, calls that plan for themselves over a fixed
-// layout) mark their K/V loads nontemporal: `key_rows` and `readers` as above,
-// from half the MALL on.
-bool streams_kv(double key_rows, int readers);
-
 // One entry of the configuration-specific split table (policies TABLE and
 // TABLE_STREAMED): the launch measured fastest on one shape of a calibration
 // sweep.

@@ -52,17 +52,17 @@ def test_argument_errors(kw, code):
     assert call(**kw) == code
 
 
-def test_mixed_schedules_stream_beyond_half_the_mall():
-    """A schedule of mixed lengths marks its K/V loads nontemporal above 128
-    MiB where one workgroup reads each key; equal lengths keep the uniform
-    plan's line (288 MiB)."""
-    at = (128 << 20) // (512 * 8)               # keys of 8 KV heads in 128 MiB
+def test_mixed_schedules_stream_beyond_the_mall():
+    """A schedule marks its K/V loads nontemporal above 288 MiB where one
+    workgroup reads each key, of mixed lengths as of equal ones: below, the
+    hint slows a call that finds its K/V in the MALL."""
+    at = (288 << 20) // (512 * 8)               # keys of 8 KV heads in 288 MiB
     for keys, want in ((at - 4096, 0), (at + 4096, 1)):
         lens = [keys - 10 * 2000 - 7] + [2000] * 10
         sched, _ = da.da_make_schedule(lens, 64, 8, num_cus=256)
         assert sched.kv_nontemporal == want
-    equal, _ = da.da_make_schedule([at // 8 + 32] * 8, 64, 8, num_cus=256)
-    shared, _ = da.da_make_schedule([at * 2, 3000], 128, 2, num_cus=256)      # two head tiles read each key
+    equal, _ = da.da_make_schedule([at // 8 - 32] * 8, 64, 8, num_cus=256)
+    shared, _ = da.da_make_schedule([at * 5, 3000], 128, 2, num_cus=256)      # two head tiles read each key
     assert equal.kv_nontemporal == 0 and shared.kv_nontemporal == 0
 
 
