@@ -331,9 +331,6 @@ int da_decode_attn_paged_planned(const void* q, const void* k_cache, const void*
                                  float softmax_scale, const da_plan* plan, void* workspace,
                                  size_t workspace_bytes, void* stream);
 
-/* See da_schedule.kv_fetch. */
-#define DA_SCHEDULE_DEALT 4
-
 /* Per-sequence scheduler metadata: the precomputed scheduling of Section 5.1
  * carried down to one split count per sequence, so that in a batch of mixed
  * lengths long sequences are cut into more chunks than short ones (the
@@ -350,11 +347,7 @@ typedef struct da_schedule {
   int32_t max_splits;            /* largest per-sequence split count (1..64) */
   int32_t state_rows;            /* chunk-state rows: sum of s_b over sequences with s_b > 1 */
   int32_t num_cus;               /* compute units planned for (after cu_margin) */
-  int32_t kv_fetch;              /* as in da_plan; plus DA_SCHEDULE_DEALT where the schedule, of mixed
-                                    lengths and chosen chunks, is long enough that the launch shares
-                                    the tiles of the lengths on the device evenly instead
-                                    (da_decode_attn_dealt), with combine 1; clear it, or combine,
-                                    to run the chunks listed */
+  int32_t kv_fetch;              /* as in da_plan */
   int32_t seq_offset;            /* byte offset of the per-sequence table in the metadata */
   int32_t meta_bytes;            /* metadata bytes written */
   int32_t kv_nontemporal;        /* as in da_plan, for the K/V of all B sequences */

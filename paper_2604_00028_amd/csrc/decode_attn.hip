@@ -1311,12 +1311,9 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(1, 
     if (b < p.B) {
       if constexpr (PG) {
         len = p.seq_lens[b];
-      } else if (p.cu) {
+      } else {
         row = p.cu[b];
         len = p.cu[b + 1] - row;
-      } else {
-        row = b * p.L_K;  // fixed layout (2^31 rows are more than the memory holds)
-        len = p.L_K;
       }
     }
     win = b0;
@@ -1924,27 +1921,6 @@ int launch_dealt(const Params& prm, const da::DealtPlan& dp, hipStream_t stream)
   return DA_OK;
 }
 
-// The dealt launch of checked arguments; `p` carries the K/V layout.
-int run_dealt(Params p, const da::DealtPlan& dp, int B, int H_Q, int H_KV, int L_K_max, float softmax_scale, void* out,
-              float* lse_out, void* workspace, size_t workspace_bytes, void* stream) {
-  da_plan pl{};
-  pl.num_splits = 1;
-  pl.heads_per_tile = dp.heads_per_tile;
-  pl.tiles = B * (H_Q / dp.heads_per_tile);
-  fill_params(p, B, H_Q, H_KV, L_K_max, softmax_scale, pl);
-  p.groups = dp.groups;
-  p.mode = kFused;
-  p.out = static_cast<uint16_t*>(out);
-  p.lse = lse_out;
-  const da::WorkspaceLayout wl = da::workspace_layout(2 * dp.groups, H_Q, D, 1);
-  unsigned char* ws = static_cast<unsigned char*>(workspace);
-  p.o_part = reinterpret_cast<float*>(ws + wl.o_off);
-  p.m_part = reinterpret_cast<float*>(ws + wl.m_off);
-  p.l_part = reinterpret_cast<float*>(ws + wl.l_off);
-  p.arrivals = reinterpret_cast<uint32_t*>(ws + da::arrival_offset(workspace_bytes));
-  return launch_dealt(p, dp, static_cast<hipStream_t>(stream));
-}
-
 // Checks of the paged layout arguments (shape already checked).
 int check_paged(const void* q, const void* k_cache, const void* v_cache, const int32_t* block_table,
                 const int32_t* seq_lens, int B, int page_size, int max_pages, int num_pages, int L_K_max) {
@@ -2186,8 +2162,7 @@ int da_decode_attn_scheduled(const void* q, const void* k, const void* v, const 
   if (!da::heads_per_tile_valid(H_Q, H_KV, sched->pack_gqa, hpt) ||
       sched->tiles != B * (H_Q / hpt) || sched->num_items < sched->tiles ||
       (int64_t)sched->num_items > (int64_t)sched->tiles * DA_MAX_SPLITS || sched->max_splits < 1 ||
-      sched->max_splits > DA_MAX_SPLITS || sched->state_rows < 0 ||
-      sched->kv_fetch < 0 || (sched->kv_fetch & ~DA_SCHEDULE_DEALT) > 2 ||
+      sched->max_splits > DA_MAX_SPLITS || sched->state_rows < 0 || sched->kv_fetch < 0 || sched->kv_fetch > 2 ||
       sched->kv_nontemporal < 0 || sched->kv_nontemporal > 1 ||
       (int64_t)sched->seq_offset != (int64_t)sched->num_items * 16 ||
       (sched->max_splits > 1) != (sched->state_rows > 0) || sched->combine < 0 || sched->combine > 1 ||
@@ -2218,9 +2193,6 @@ int da_decode_attn_scheduled(const void* q, const void* k, const void* v, const 
     p.v = static_cast<const uint16_t*>(v);
     p.cu = cu_seqlens_k;
   }
-  da::DealtPlan dp;
-  if (da::schedule_dealt(*sched, &dp))
-    return run_dealt(p, dp, B, H_Q, H_KV, L_K_max, softmax_scale, out, lse_out, workspace, workspace_bytes, stream);
   da_plan pl{};
   pl.num_splits = 1;
   pl.pack_gqa = sched->pack_gqa;
@@ -2229,7 +2201,7 @@ int da_decode_attn_scheduled(const void* q, const void* k, const void* v, const 
   pl.grid = sched->num_items;
   pl.num_cus = sched->num_cus;
   pl.group_waves = 4;
-  pl.kv_fetch = sched->kv_fetch & ~DA_SCHEDULE_DEALT;
+  pl.kv_fetch = sched->kv_fetch;
   pl.kv_nontemporal = sched->kv_nontemporal;
   pl.v_slices = 1;
   pl.combine = 0;
@@ -2281,9 +2253,9 @@ int da_decode_attn_dealt(const void* q, const void* k, const void* v, const int3
   da::DealtPlan dp;
   if (!da::dealt_plan(B, H_Q, H_KV, L_K_max, keys, cus, &dp))
     return da::fail(DA_ERR_ARG, "B=%d H_Q=%d H_KV=%d is not a shape the dealt launch takes", B, H_Q, H_KV);
-  const size_t need = da::workspace_layout(2 * dp.groups, H_Q, d, 1).total;
-  if (workspace_bytes < need)
-    return da::fail(DA_ERR_WORKSPACE, "the dealt launch needs %zu workspace bytes, got %zu", need, workspace_bytes);
+  const da::WorkspaceLayout wl = da::workspace_layout(2 * dp.groups, H_Q, d, 1);
+  if (workspace_bytes < wl.total)
+    return da::fail(DA_ERR_WORKSPACE, "the dealt launch needs %zu workspace bytes, got %zu", wl.total, workspace_bytes);
   Params p{};
   if (block_table) {
     set_paged(p, q, k, v, block_table, seq_lens, page_size, max_pages, num_pages);
@@ -2293,7 +2265,21 @@ int da_decode_attn_dealt(const void* q, const void* k, const void* v, const int3
     p.v = static_cast<const uint16_t*>(v);
     p.cu = cu_seqlens_k;
   }
-  return run_dealt(p, dp, B, H_Q, H_KV, L_K_max, softmax_scale, out, lse_out, workspace, workspace_bytes, stream);
+  da_plan pl{};
+  pl.num_splits = 1;
+  pl.heads_per_tile = dp.heads_per_tile;
+  pl.tiles = B * (H_Q / dp.heads_per_tile);
+  fill_params(p, B, H_Q, H_KV, L_K_max, softmax_scale, pl);
+  p.groups = dp.groups;
+  p.mode = kFused;
+  p.out = static_cast<uint16_t*>(out);
+  p.lse = lse_out;
+  unsigned char* ws = static_cast<unsigned char*>(workspace);
+  p.o_part = reinterpret_cast<float*>(ws + wl.o_off);
+  p.m_part = reinterpret_cast<float*>(ws + wl.m_off);
+  p.l_part = reinterpret_cast<float*>(ws + wl.l_off);
+  p.arrivals = reinterpret_cast<uint32_t*>(ws + da::arrival_offset(workspace_bytes));
+  return launch_dealt(p, dp, static_cast<hipStream_t>(stream));
 }
 
 int da_split_partials(const void* q, const void* k, const void* v, const int32_t* cu_seqlens_k, float* o_part,

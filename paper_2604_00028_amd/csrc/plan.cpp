@@ -735,21 +735,6 @@ int make_schedule(const int32_t* seq_lens, int B, int H_Q, int H_KV, int L_K_max
   {
     double key_rows = 0.0;
     for (int b = 0; b < B; ++b) key_rows += (double)seq_lens[b] * H_KV;
-    // Chosen schedules of long shares run as the dealt launch: one round of
-    // even shares, two waves each, instead of chunks of one length in about
-    // five.  Measured on 60 mixed batches: from 128 tiles a share on
-    // 1.01-1.07x faster (32 sequences of 1024 to 16384 keys over 8 KV heads:
-    // 174 -> 164 us), below 100 0.4-1.0x; passing from one sequence to the
-    // next costs as much as three or four tiles, so short sequences take longer
-    // shares still (116 of them, bimodal, 98 tiles: 0.88x).
-    DealtPlan dp;
-    if (chunk_tiles <= 0 && !equal && pack == (g > 1 ? 1 : 0) && hpt == g && hpt <= kNarrowHeadsPerTile && out->combine == 1 &&
-        dealt_plan(B, H_Q, H_KV, L_K_max, 0, cus, &dp) && dp.heads_per_tile == hpt) {
-      int64_t all = 0;
-      for (int b = 0; b < B; ++b) all += std::max<int64_t>(1, T[b]);
-      const int64_t share = all / dp.groups;
-      if (share >= 128 && share >= 40 * (int64_t)B / dp.groups) out->kv_fetch |= DA_SCHEDULE_DEALT;
-    }
     out->kv_nontemporal = kv_nontemporal(key_rows, g / hpt);
   }
   if (!meta) return fail(DA_ERR_NULL, "meta is NULL");
@@ -852,14 +837,6 @@ bool prefers_dealt(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int cus)
   return share >= (wide ? 32 : 16) && longest >= (wide ? 2.9 : 2.2) * share;
 }
 
-bool schedule_dealt(const da_schedule& s, DealtPlan* out) {
-  if (!(s.kv_fetch & DA_SCHEDULE_DEALT) || s.combine != 1 || s.state_rows <= 0) return false;
-  if (!dealt_plan(s.B, s.H_Q, s.H_KV, s.L_K_max, 0, s.num_cus, out) || out->heads_per_tile != s.heads_per_tile)
-    return false;
-  out->kv_nontemporal = s.kv_nontemporal;
-  return true;
-}
-
 WorkspaceLayout workspace_layout(int B, int H_Q, int d, int s) {
   WorkspaceLayout w{};
   const size_t rows = (size_t)B * H_Q;
@@ -931,13 +908,7 @@ int da_make_schedule(const int32_t* seq_lens, int B, int H_Q, int H_KV, int L_K_
 
 size_t da_schedule_workspace_bytes(const da_schedule* s) {
   if (!s || s->state_rows <= 0 || s->H_Q <= 0) return 0;
-  const size_t states = da::workspace_layout(s->state_rows, s->H_Q, da::kHeadDim, 1).total;
-  // a dealt schedule whose merge is edited out runs its own chunks, so it holds either
-  da::DealtPlan dp;
-  da_schedule fused = *s;
-  fused.combine = 1;
-  if (!da::schedule_dealt(fused, &dp)) return states;
-  return std::max(states, da::workspace_layout(2 * dp.groups, s->H_Q, da::kHeadDim, 1).total);
+  return da::workspace_layout(s->state_rows, s->H_Q, da::kHeadDim, 1).total;
 }
 
 int da_prefers_dealt(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int num_cus) {

@@ -221,10 +221,6 @@ bool dealt_plan(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int cus, De
 // launched with one split count for all.
 bool prefers_dealt(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int cus);
 
-// Whether a schedule runs as the dealt launch (DA_SCHEDULE_DEALT and the
-// merge in the launch), and that launch.
-bool schedule_dealt(const da_schedule& s, DealtPlan* out);
-
 // Workspace regions (256-byte aligned): chunk states Otilde | m | l from
 // offset 0 (`states` ends them), and the arrival counters of single-launch
 // merges in the last DA_ARRIVAL_BYTES of the caller's buffer, wherever its

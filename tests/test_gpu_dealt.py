@@ -113,43 +113,6 @@ def test_planning_entries_deal_a_mixed_batch(page):
         assert torch.equal(got.view(torch.int16), dealt().view(torch.int16)), f"replay {r}"
 
 
-@pytest.mark.parametrize("layout", ["fixed", "varlen", "paged"])
-def test_dealt_schedule(layout):
-    """A schedule marked DA_SCHEDULE_DEALT runs the dealt launch over the
-    lengths the device holds (some other than those scheduled), in every
-    layout; with its merge taken out it runs its own chunks."""
-    H_Q, H_KV = 16, 2
-    dev_lens = [1500] * 5 if layout == "fixed" else [700, 1, 333, 1500, 0]
-    inp = make_inputs(custom_shape(5, H_Q, H_KV, 1500, varlen=layout != "fixed"), seed=71,
-                      lengths=None if layout == "fixed" else dev_lens)
-    O, lse = decode_attention(inp.q, inp.k, inp.v, inp.lengths, inp.cu_seqlens_k)
-    q, k, v, cu = dev_inputs(inp)
-    kw = {} if layout == "fixed" else dict(cu_seqlens_k=cu)
-    if layout == "paged":
-        pg = paged_layout(inp, 64, seed=8)
-        k, v = to_dev(pg.k_cache), to_dev(pg.v_cache)
-        kw = dict(block_table=torch.from_numpy(pg.block_table).cuda(), seq_lens=torch.from_numpy(pg.seq_lens).cuda())
-    sched, meta = da.da_make_schedule([300, 40, 333, 1500, 90], H_Q, H_KV, 1500, chunk_tiles=4)
-    assert sched.state_rows > 0
-    sched.combine = 1
-    meta = meta.cuda()
-    for mark in (4, 0):
-        sched.kv_fetch = sched.kv_fetch % 4 + mark
-        need = da.da_schedule_workspace_bytes(sched)
-        assert need >= (da.da_dealt_workspace_bytes(5, H_Q, H_KV) if mark else 1)
-        for combine in (1, 0):
-            sched.combine = combine
-            say(f"dealt schedule {layout} mark={mark} combine={combine}")
-            ws = torch.zeros(need, dtype=torch.uint8, device="cuda")
-            lse_t = torch.empty(5, H_Q, dtype=torch.float32, device="cuda")
-            out = da.da_decode_attn_scheduled(q, k, v, sched, meta, lse_out=lse_t, workspace=ws, **kw)
-            torch.cuda.synchronize()
-            check(out, lse_t, O, lse, f"dealt schedule {layout} mark={mark} combine={combine}")
-            if mark and combine and layout != "fixed":
-                same = da.da_decode_attn_dealt(q, k, v, 1500, **kw)
-                assert torch.equal(out.view(torch.int16), same.view(torch.int16))
-
-
 @pytest.mark.parametrize("page", [None, 64])
 @pytest.mark.parametrize("H_Q,H_KV,lengths,scale", [
     (64, 8, [8192, 3000, 6001], 2.0), (8, 1, [20000, 700], 2.0), (16, 2, [5000] * 6, 1.0), (32, 1, [4100, 9000], 1.0)])
