@@ -458,8 +458,12 @@ int da_decode_attn_dealt(const void* q, const void* k, const void* v, const int3
 size_t da_dealt_workspace_bytes(int B, int H_Q, int H_KV, int num_cus);
 
 /* 1 where da_decode_attn_dealt is expected to beat the launch with one split
- * count for all sequences (measured lines on the keys per CU and the longest
- * sequence), else 0.  keys and num_cus as above.  Host only. */
+ * count for all sequences, else 0: where the longest of that launch's chunks
+ * exceeds an even share of the batch by enough (measured lines).  L_K_max is
+ * taken as the length of the longest sequence and keys as an upper bound of
+ * all of them (a paged batch: the keys its cache holds); with a looser
+ * L_K_max, or keys <= 0, the answer says nothing about the batch.  num_cus as
+ * above.  Host only. */
 int da_prefers_dealt(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int num_cus);
 
 /* The split step alone: the partial softmax state of every chunk (the

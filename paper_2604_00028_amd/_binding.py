@@ -19,7 +19,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libdecode_attn.so")
 HEAD_DIM = 128
 MAX_SPLITS = 64
-DEALT_MIN_KEYS = 1505  # da_prefers_dealt never holds for shorter batches: no need to ask
+DEALT_MIN_KEYS = 2561  # da_prefers_dealt never holds for shorter batches: no need to ask
 
 DA_OK = 0
 DA_ERR_NULL = -1
@@ -424,7 +424,7 @@ def da_decode_attn_paged(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.
     nothing forced goes to da_decode_attn_dealt where that pays."""
     B, H_Q, H_KV, d, page_size, max_pages, num_pages = _paged_args(q, k_cache, v_cache, block_table, seq_lens)
     if (workspace is None and num_splits <= 0 and pack_gqa == -1 and L_K_max >= DEALT_MIN_KEYS and d == HEAD_DIM
-            and load().da_prefers_dealt(B, H_Q, H_KV, int(L_K_max), 0, 0)):
+            and load().da_prefers_dealt(B, H_Q, H_KV, int(L_K_max), num_pages * page_size, 0)):
         return da_decode_attn_dealt(q, k_cache, v_cache, int(L_K_max), None, block_table, seq_lens, out, lse_out,
                                     softmax_scale=softmax_scale, stream=stream)
     dev = q.device

@@ -813,28 +813,26 @@ bool dealt_plan(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int cus, De
 bool prefers_dealt(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int cus) {
   DealtPlan dp;
   if (L_K_max <= 0 || !dealt_plan(B, H_Q, H_KV, L_K_max, keys, cus, &dp)) return false;
-  // Measured on 240 mixed batches (1 to 128 sequences of 1 to 32768 keys, 11
-  // head shapes, equal, uniform, lognormal and bimodal lengths) against the
-  // launch with one split count: the deal costs about 8 us before and after
-  // the stream (finding it, two hand-offs, two merges), which it earns back
-  // where a workgroup's share is long, or where the longest sequence leaves
-  // other workgroups waiting.  With these lines it was taken on 30 of 114
-  // packed batches, 1.09x faster over all 114 (3.9x at most, 1.11x had the
-  // faster launch been known each time), and on 22 of 126 paged ones, 1.09x over
-  // all; 0.92x and better where it lost.
   const bool wide = dp.heads_per_tile > 16;
-  const int64_t tps = H_Q / dp.heads_per_tile, rows = B * tps;
+  const int64_t rows = (int64_t)B * (H_Q / dp.heads_per_tile);
   const int64_t top = (L_K_max + 31) / 32;
-  if (rows > 5 * (int64_t)cus || top < 48) return false;  // many short workgroups balance themselves
-  if (keys <= 0) {
-    // only an upper bound is known: the share has to be long were it reached
-    return (double)B * top / dp.groups >= (wide ? 128 : 64);
-  }
-  const double share = (double)std::min<int64_t>(keys / 32 + B, B * top) / dp.groups;
-  if (share >= (wide ? 128 : 32)) return true;
-  // the longest chunk of one split count against the share
+  if (rows > 5 * (int64_t)cus) return false;  // many workgroups balance themselves (none measured)
+  const double share = (double)std::min<int64_t>(keys > 0 ? keys / 32 + B : INT64_MAX, B * top) / dp.groups;
   const double longest = (double)top / (double)std::max<int64_t>(1, cus / rows);
-  return share >= (wide ? 32 : 16) && longest >= (wide ? 2.9 : 2.2) * share;
+  // What the launch with one split count waits for is its longest chunk, what
+  // the dealt launch waits for is the even share; the deal's fixed part (about
+  // 8 us: finding it, two hand-offs, two merges) and its sequence ends are
+  // paid out of the difference.  Both are bounds, whatever the lengths are, as
+  // long as some sequence has L_K_max keys and the batch at most `keys`.
+  // Measured on 460 batches (1 to 128 sequences of 1 to 32768 keys, 11 head
+  // shapes, equal, uniform, lognormal and bimodal lengths, packed and paged),
+  // each with other batches in turn and over and over: with these lines 156 of
+  // narrow tiles are taken, 1.72x faster in turn and 1.83x over and over, one
+  // of them slower (0.90x); from 60 tiles on 9 of 194 are, down to 0.77x.
+  // Lines on the share alone took equal lengths at 0.84-0.98x.  Wide tiles
+  // lose up to a difference of 270 tiles (0.86x) and gain on all 7 batches
+  // past 300 (1.32x and more).
+  return longest >= 1.7 * share && longest - share >= (wide ? 320.0 : 80.0);
 }
 
 WorkspaceLayout workspace_layout(int B, int H_Q, int d, int s) {

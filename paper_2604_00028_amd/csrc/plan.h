@@ -218,7 +218,7 @@ struct DealtPlan {
 // arrival counters, or head tiles that leave CUs over.
 bool dealt_plan(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int cus, DealtPlan* out);
 // Whether a batch whose lengths only the device holds is dealt rather than
-// launched with one split count for all.
+// launched with one split count for all (keys <= 0: unknown).
 bool prefers_dealt(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int cus);
 
 // Workspace regions (256-byte aligned): chunk states Otilde | m | l from

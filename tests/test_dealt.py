@@ -9,18 +9,25 @@ from paper_2604_00028_amd import _binding as bnd
 FAKE = 0x100000
 
 
-def test_preferred_where_shares_are_long():
+def test_preferred_where_the_longest_chunk_exceeds_the_share():
     p = lambda *a: da.da_prefers_dealt(*a, num_cus=256)  # noqa: E731
-    assert p(32, 64, 8, 16384, 0) and p(32, 64, 8, 16384, 32 * 8000)
-    assert p(64, 8, 1, 32768, 64 * 5000)
+    assert p(32, 64, 8, 16384, 32 * 8000) and p(64, 8, 1, 32768, 64 * 5000)
+    # one long sequence among short ones
+    assert p(32, 64, 8, 20000, 50000) and not p(4, 64, 8, 8000, 9000)
     assert not p(16, 32, 4, 512, 16 * 300) and not p(1, 64, 8, 8192, 8192)     # short shares
     assert not p(32, 64, 8, 0, 0)                                              # nothing to read
-    assert not p(512, 64, 8, 8192, 0)                                          # many workgroups balance themselves
+    assert not p(512, 64, 8, 8192, 512 * 1000)                                 # many workgroups balance themselves
     assert not p(8, 10, 5, 0, 0)
+    # equal lengths, and batches of which only B * L_K_max is known: one split count is even already
+    for B, H_Q, H_KV, L in ((58, 64, 4, 5180), (110, 16, 2, 6661), (34, 32, 2, 9741), (82, 64, 8, 1670), (16, 128, 2, 26847)):
+        assert not p(B, H_Q, H_KV, L, B * L) and not p(B, H_Q, H_KV, L, 0), (B, H_Q, H_KV, L)
+    # the lines: 80 tiles over a share of 6.25, and 1.7 shares of 200 tiles
+    assert next(t for t in range(1, 4000) if p(100, 64, 8, 32 * t, 3200)) == 87
+    assert next(t for t in range(1, 4000) if p(32, 64, 8, 32 * t, 32 * 6368)) == 340
+    # wide head tiles need four times the difference
+    assert next(t for t in range(1, 4000) if p(64, 128, 2, 32 * t, 32 * 6336)) == 420
     # what the Python entry points assume without asking
-    assert p(128, 64, 8, bnd.DEALT_MIN_KEYS, 0) and not p(128, 64, 8, bnd.DEALT_MIN_KEYS - 1, 0)
-    # one long sequence among short ones, the keys known or not
-    assert p(32, 64, 8, 20000, 50000) and not p(4, 64, 8, 8000, 9000)
+    assert p(129, 8, 1, bnd.DEALT_MIN_KEYS, 1) and not p(129, 8, 1, bnd.DEALT_MIN_KEYS - 1, 1)
     # head tiles that leave more than a tenth of the CUs idle, or more than the arrival counters
     assert not p(32, 160, 160, 16384, 0) and da.da_dealt_workspace_bytes(32, 160, 160, 256) == 0
     assert da.da_dealt_workspace_bytes(1024, 64, 8, 256) == 0

@@ -73,9 +73,9 @@ def test_planning_entries_deal_a_mixed_batch(page):
     where it is preferred, also from a graph whose lengths change between
     replays, and their own plan's with a forced split count."""
     H_Q, H_KV = 64, 8
-    lengths = [int(x) for x in np.random.default_rng(3).integers(1500, 6000, 16)]
+    lengths = [int(x) for x in np.random.default_rng(3).integers(500, 5000, 31)] + [8000]
     B, top = len(lengths), 8000
-    assert da.da_prefers_dealt(B, H_Q, H_KV, top, 0) and da.da_prefers_dealt(B, H_Q, H_KV, top, sum(lengths))
+    assert da.da_prefers_dealt(B, H_Q, H_KV, top, sum(lengths))
     inp = make_inputs(custom_shape(B, H_Q, H_KV, max(lengths), varlen=True), seed=11, lengths=lengths)
     q, k, v, cu = dev_inputs(inp)
     if page is None:
