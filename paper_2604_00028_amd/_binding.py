@@ -248,6 +248,18 @@ def _stream(dev: torch.device, stream) -> int:
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
+def _on(dev: torch.device, handle: int) -> torch.cuda.Stream:
+    return torch.cuda.ExternalStream(handle, device=dev) if handle else torch.cuda.default_stream(dev)
+
+
+def _capturing(dev: torch.device, stream) -> bool:
+    """Whether a call's stream (None: the current one) is being captured into a graph."""
+    if stream is None and dev.index == torch.cuda.current_device():
+        return torch.cuda.is_current_stream_capturing()
+    with torch.cuda.stream(_on(dev, _stream(dev, stream))):
+        return torch.cuda.is_current_stream_capturing()
+
+
 def _new_out(q: torch.Tensor) -> torch.Tensor:
     return torch.empty_like(q, memory_format=torch.contiguous_format)
 
@@ -313,8 +325,7 @@ def workspace_for(dev: torch.device, stream_handle: int, nbytes: int) -> torch.T
         _workspaces[key] = ws
         if dev.type == "cuda" and stream_handle != torch.cuda.current_stream(dev).cuda_stream:
             # the fill runs on torch's current stream: the call's own stream waits for it
-            own = torch.cuda.ExternalStream(stream_handle, device=dev) if stream_handle else torch.cuda.default_stream(dev)
-            own.wait_stream(torch.cuda.current_stream(dev))
+            _on(dev, stream_handle).wait_stream(torch.cuda.current_stream(dev))
     return ws
 
 
@@ -330,15 +341,25 @@ def _nbytes(t: Optional[torch.Tensor]) -> int:
     return t.numel() * t.element_size() if t is not None else 0
 
 
+def _deals(B: int, H_Q: int, H_KV: int, L: int, keys: int, dev: torch.device, stream) -> bool:
+    """Whether a batch whose lengths the device holds goes to
+    da_decode_attn_dealt.  Not while a graph is captured: its replays follow
+    other lengths, for which L_K_max is a bound and not the longest sequence
+    (78 sequences of 100-550 keys under L_K_max 32768: 8.2 us, dealt 14.9),
+    and a workspace allocated then would be cleared by the replays only."""
+    return load().da_prefers_dealt(B, H_Q, H_KV, L, keys, 0) != 0 and not _capturing(dev, stream)
+
+
 def da_decode_attn(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, cu_seqlens_k: Optional[torch.Tensor] = None,
                    out: Optional[torch.Tensor] = None, lse_out: Optional[torch.Tensor] = None, *,
                    L_K_max: Optional[int] = None, softmax_scale: float = 0.0, num_splits: int = 0,
                    pack_gqa: int = -1, workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """O = softmax(scale q K^T) V for one decode step; returns `out`.  A packed
-    batch with nothing forced goes to da_decode_attn_dealt where that pays."""
+    batch with nothing forced and no workspace passed goes to
+    da_decode_attn_dealt where that pays, outside graph capture."""
     B, H_Q, H_KV, L, d = _shapes(q, k, v, cu_seqlens_k, L_K_max)
     if (cu_seqlens_k is not None and workspace is None and num_splits <= 0 and pack_gqa == -1
-            and L >= DEALT_MIN_KEYS and d == HEAD_DIM and load().da_prefers_dealt(B, H_Q, H_KV, L, k.shape[0], 0)):
+            and L >= DEALT_MIN_KEYS and d == HEAD_DIM and _deals(B, H_Q, H_KV, L, k.shape[0], q.device, stream)):
         return da_decode_attn_dealt(q, k, v, L, cu_seqlens_k, out=out, lse_out=lse_out, softmax_scale=softmax_scale,
                                     stream=stream)
     dev = q.device
@@ -421,10 +442,11 @@ def da_decode_attn_paged(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.
     """Decode attention over a paged KV cache; returns `out`.
     k_cache, v_cache: [num_pages, page_size, H_KV, d] bf16; block_table: [B, max_pages] int32;
     seq_lens: [B] int32; L_K_max: host-known longest sequence.  A batch with
-    nothing forced goes to da_decode_attn_dealt where that pays."""
+    nothing forced and no workspace passed goes to da_decode_attn_dealt where
+    that pays, outside graph capture."""
     B, H_Q, H_KV, d, page_size, max_pages, num_pages = _paged_args(q, k_cache, v_cache, block_table, seq_lens)
     if (workspace is None and num_splits <= 0 and pack_gqa == -1 and L_K_max >= DEALT_MIN_KEYS and d == HEAD_DIM
-            and load().da_prefers_dealt(B, H_Q, H_KV, int(L_K_max), num_pages * page_size, 0)):
+            and _deals(B, H_Q, H_KV, int(L_K_max), num_pages * page_size, q.device, stream)):
         return da_decode_attn_dealt(q, k_cache, v_cache, int(L_K_max), None, block_table, seq_lens, out, lse_out,
                                     softmax_scale=softmax_scale, stream=stream)
     dev = q.device

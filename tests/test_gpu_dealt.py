@@ -70,8 +70,9 @@ def test_dealt_parity(H_Q, H_KV, lengths, page):
 @pytest.mark.parametrize("page", [None, 64])
 def test_planning_entries_deal_a_mixed_batch(page):
     """da_decode_attn and da_decode_attn_paged give the dealt launch's bits
-    where it is preferred, also from a graph whose lengths change between
-    replays, and their own plan's with a forced split count."""
+    where it is preferred, and their own plan's with a forced split count or
+    while a graph is captured; a captured da_decode_attn_dealt follows the
+    lengths from replay to replay."""
     H_Q, H_KV = 64, 8
     lengths = [int(x) for x in np.random.default_rng(3).integers(500, 5000, 31)] + [8000]
     B, top = len(lengths), 8000
@@ -79,13 +80,13 @@ def test_planning_entries_deal_a_mixed_batch(page):
     inp = make_inputs(custom_shape(B, H_Q, H_KV, max(lengths), varlen=True), seed=11, lengths=lengths)
     q, k, v, cu = dev_inputs(inp)
     if page is None:
-        call = lambda s: da.da_decode_attn(q, k, v, cu, L_K_max=top, num_splits=s)  # noqa: E731
+        call = lambda s, ws=None: da.da_decode_attn(q, k, v, cu, L_K_max=top, num_splits=s, workspace=ws)  # noqa: E731
         dealt = lambda: da.da_decode_attn_dealt(q, k, v, top, cu)  # noqa: E731
     else:
         pg = paged_layout(inp, page, seed=5, max_pages=-(-top // page))
         k, v = to_dev(pg.k_cache), to_dev(pg.v_cache)
         bt, sl = torch.from_numpy(pg.block_table).cuda(), torch.from_numpy(pg.seq_lens).cuda()
-        call = lambda s: da.da_decode_attn_paged(q, k, v, bt, sl, top, num_splits=s)  # noqa: E731
+        call = lambda s, ws=None: da.da_decode_attn_paged(q, k, v, bt, sl, top, num_splits=s, workspace=ws)  # noqa: E731
         dealt = lambda: da.da_decode_attn_dealt(q, k, v, top, block_table=bt, seq_lens=sl)  # noqa: E731
     say(f"dealt route page={page}")
     a, b, forced = call(0), dealt(), call(2)
@@ -97,20 +98,25 @@ def test_planning_entries_deal_a_mixed_batch(page):
         O, _ = decode_attention(inp.q[s:s + 1], inp.k[cuh[s]:cuh[s + 1]][None], inp.v[cuh[s]:cuh[s + 1]][None])
         assert_parity(a[s:s + 1], O, f"dealt route sequence {s}")
         assert_parity(forced[s:s + 1], O, f"forced splits sequence {s}")
-    if page is None:
-        return
+    # the plan the entry point makes for itself, which a workspace of the caller's keeps
+    plan_ws = torch.zeros(da.da_workspace_bytes(B, H_Q, 128, 64), dtype=torch.uint8, device="cuda")
+    own = lambda: call(0, plan_ws)  # noqa: E731
+    assert not torch.equal(a.view(torch.int16), own().view(torch.int16))
+    torch.cuda.synchronize()
     stream = torch.cuda.Stream()
     with torch.cuda.stream(stream):
-        call(0)                         # workspace of this stream
+        call(0), call(2), dealt()       # workspace of this stream
     stream.synchronize()
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g, stream=stream):
-        got = call(0)
+        got, got_dealt = call(0), dealt()
     for r in range(4):
-        sl.copy_(torch.from_numpy(pg.seq_lens) - 37 * r)
+        if page is not None:
+            sl.copy_(torch.from_numpy(pg.seq_lens) - 37 * r)
         g.replay()
         torch.cuda.synchronize()
-        assert torch.equal(got.view(torch.int16), dealt().view(torch.int16)), f"replay {r}"
+        assert torch.equal(got.view(torch.int16), own().view(torch.int16)), f"replay {r}"
+        assert torch.equal(got_dealt.view(torch.int16), dealt().view(torch.int16)), f"dealt replay {r}"
 
 
 @pytest.mark.parametrize("page", [None, 64])
