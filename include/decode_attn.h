@@ -426,20 +426,21 @@ int da_decode_attn_scheduled(const void* q, const void* k, const void* v,
 /* Decode attention over a batch of mixed lengths that only the device holds:
  * the same result as da_decode_attn with cu_seqlens_k, or as
  * da_decode_attn_paged, up to rounding order, in one launch that shares the
- * batch's 32-key tiles evenly among the CUs instead of cutting every sequence
- * into one number of chunks.  The workgroups read the lengths and find the
+ * batch's 32-key tiles evenly among the CUs (of a CU-masked stream, those it
+ * has) instead of cutting every sequence into one number of chunks.  The workgroups read the lengths and find the
  * deal themselves: each takes a run of consecutive tiles of the batch, which
  * may end one sequence, hold others and begin the next; sequences that two or
  * more workgroups share are merged inside the launch.  No length is read on
  * the host, nothing is allocated, the call can be captured, and replays follow
  * the lengths the device then holds (each at most L_K_max).  Results are
- * bit-identical across runs for the same lengths.
+ * bit-identical across runs for the same lengths of the whole batch and the
+ * same number of CUs, which decide where each sequence is cut.
  *   block_table == NULL: k, v packed as for da_decode_attn with cu_seqlens_k
  *     (page_size, max_pages, num_pages, seq_lens ignored); otherwise paged as
  *     for da_decode_attn_paged (cu_seqlens_k ignored)
  *   keys       keys of the whole batch or an upper bound, if the host knows
- *              one (packed: the rows of k); <= 0 otherwise.  It picks the
- *              cache hint, never the result
+ *              one (packed: the rows of k); <= 0: B * L_K_max.  It picks the
+ *              cache hint (as da_plan.kv_nontemporal), never the result
  *   workspace  >= da_dealt_workspace_bytes(B, H_Q, H_KV, 0): chunk states and
  *              the counter region, zero before the first call as for
  *              da_decode_attn; every call leaves it zero
@@ -454,7 +455,8 @@ int da_decode_attn_dealt(const void* q, const void* k, const void* v, const int3
                          void* stream);
 
 /* Workspace bytes da_decode_attn_dealt needs for this shape (num_cus 0: query
- * the current device); 0 for a shape it does not take. */
+ * the current device, which is enough for any of its streams); 0 for a shape
+ * it does not take. */
 size_t da_dealt_workspace_bytes(int B, int H_Q, int H_KV, int num_cus);
 
 /* 1 where da_decode_attn_dealt is expected to beat the launch with one split

@@ -54,6 +54,7 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <type_traits>
@@ -1653,6 +1654,20 @@ int query_device(int* cus, int* is950, int* lds = nullptr) {
   return DA_OK;
 }
 
+// CUs that kernels on `stream` may run on: the device's `cus`, or fewer on a
+// CU-masked stream (0.55 us a call).
+int stream_cus(hipStream_t stream, int cus) {
+  uint32_t mask[32];
+  const uint32_t words = ((uint32_t)cus + 31u) / 32u;
+  if (words > 32u || hipExtStreamGetCUMask(stream, words, mask) != hipSuccess) {
+    (void)hipGetLastError();
+    return cus;
+  }
+  int n = 0;
+  for (uint32_t i = 0; i < words; ++i) n += __builtin_popcount(mask[i]);
+  return n > 0 && n < cus ? n : cus;
+}
+
 bool aligned(const void* ptr, uintptr_t a) { return ((uintptr_t)ptr & (a - 1)) == 0; }
 
 int check_inputs(const void* q, const void* k, const void* v, const int32_t* cu, int B, int H_Q, int H_KV,
@@ -2253,6 +2268,9 @@ int da_decode_attn_dealt(const void* q, const void* k, const void* v, const int3
   da::DealtPlan dp;
   if (!da::dealt_plan(B, H_Q, H_KV, L_K_max, keys, cus, &dp))
     return da::fail(DA_ERR_ARG, "B=%d H_Q=%d H_KV=%d is not a shape the dealt launch takes", B, H_Q, H_KV);
+  // one share per CU the stream has: a CU left with two would hold up the rest
+  const int own = stream_cus(static_cast<hipStream_t>(stream), cus);
+  if (own < cus) dp.groups = std::max(1, own / (H_Q / dp.heads_per_tile));
   const da::WorkspaceLayout wl = da::workspace_layout(2 * dp.groups, H_Q, d, 1);
   if (workspace_bytes < wl.total)
     return da::fail(DA_ERR_WORKSPACE, "the dealt launch needs %zu workspace bytes, got %zu", wl.total, workspace_bytes);

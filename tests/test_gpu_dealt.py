@@ -149,3 +149,30 @@ def test_dealt_is_no_further_from_64_bits(H_Q, H_KV, lengths, scale, page):
     rel = [float(np.linalg.norm(to_f64(x) - O) / np.linalg.norm(O)) for x in (dealt, split)]
     say(f"  dealt {rel[0]:.3e} 16 splits {rel[1]:.3e}")
     assert rel[0] <= rel[1]
+
+
+def test_dealt_on_a_masked_stream():
+    """On a CU-masked stream the batch is dealt over the CUs the stream has:
+    a workspace for that many suffices there and not on a stream with all."""
+    from paper_2604_00028_amd.streams import cu_mask_stream, destroy_stream, split_masks
+    H_Q, H_KV, lengths = 64, 8, [3000, 17, 0, 900, 2100]
+    B, L = len(lengths), max(lengths)
+    inp = make_inputs(custom_shape(B, H_Q, H_KV, L, varlen=True), seed=29, lengths=lengths)
+    O, lse = decode_attention(inp.q, inp.k, inp.v, inp.lengths, inp.cu_seqlens_k)
+    q, k, v, cu = dev_inputs(inp)
+    cus = da.da_device_info()[0]
+    stream, enabled = cu_mask_stream(split_masks(cus, 8)[1])
+    try:
+        assert enabled < cus
+        ws = torch.zeros(da.da_dealt_workspace_bytes(B, H_Q, H_KV, enabled), dtype=torch.uint8, device="cuda")
+        lse_t = torch.empty(B, H_Q, dtype=torch.float32, device="cuda")
+        out = torch.empty(B, H_Q, 128, dtype=torch.bfloat16, device="cuda")
+        torch.cuda.synchronize()
+        say(f"dealt on {enabled} of {cus} CUs")
+        da.da_decode_attn_dealt(q, k, v, L, cu, out=out, lse_out=lse_t, workspace=ws, stream=stream)
+        torch.cuda.synchronize()
+        check(out, lse_t, O, lse, "dealt on a masked stream")
+        with pytest.raises(da.DecodeAttnError):
+            da.da_decode_attn_dealt(q, k, v, L, cu, out=out, workspace=ws)
+    finally:
+        destroy_stream(stream)
