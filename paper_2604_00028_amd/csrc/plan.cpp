@@ -802,7 +802,8 @@ bool dealt_plan(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int cus, De
   const int tps = H_Q / hpt;
   if ((int64_t)B * tps > kMaxArrivalTiles || tps > cus) return false;
   const int groups = cus / tps;
-  if (10 * groups * tps < 9 * cus) return false;  // CUs left over
+  if ((int64_t)10 * groups * tps < (int64_t)9 * cus) return false;                       // CUs left over
+  if ((int64_t)2 * groups * H_Q * kHeadDim * 4 >= (int64_t)1 << 31) return false;  // 32-bit state offsets
   out->heads_per_tile = hpt;
   out->groups = groups;
   const double most = (double)std::min<int64_t>(keys > 0 ? keys : INT64_MAX, (int64_t)B * L_K_max);

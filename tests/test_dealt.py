@@ -38,6 +38,11 @@ def test_workspace_bytes():
     # two chunk states for each of 256 / 8 workgroups of every head tile: Otilde | m | l, then the counters
     assert da.da_dealt_workspace_bytes(32, 64, 8, 256) == 2 * 32 * 64 * (128 * 4 + 4 + 4) + (1 << 20)
     assert da.da_dealt_workspace_bytes(3, 8, 1, 256) == 2 * 256 * 8 * (128 * 4 + 4 + 4) + (1 << 20)
+    # chunk states stay below 2 GiB (their offsets have 32 bits): no shape of more CUs than that
+    most = (1 << 31) // (2 * 8 * 512)
+    assert da.da_dealt_workspace_bytes(3, 8, 1, most - 1) > 0 and da.da_dealt_workspace_bytes(3, 8, 1, most) == 0
+    for cus in (1 << 28, (1 << 30) + 1, (1 << 31) - 1):
+        assert da.da_dealt_workspace_bytes(3, 8, 1, cus) == 0 and not da.da_prefers_dealt(32, 64, 8, 16384, 1000, cus)
 
 
 def call(q=FAKE, k=FAKE, v=FAKE, cu=FAKE, bt=None, sl=None, page=64, mp=8, npg=8, out=FAKE, lse=None, B=2, H_Q=8,
