@@ -321,11 +321,26 @@ def workspace_for(dev: torch.device, stream_handle: int, nbytes: int) -> torch.T
     if ws is None or ws.numel() < nbytes:
         if ws is not None:
             _retired.append(ws)
-        ws = torch.zeros(max(nbytes, 256), dtype=torch.uint8, device=dev)
-        _workspaces[key] = ws
-        if dev.type == "cuda" and stream_handle != torch.cuda.current_stream(dev).cuda_stream:
-            # the fill runs on torch's current stream: the call's own stream waits for it
-            _on(dev, stream_handle).wait_stream(torch.cuda.current_stream(dev))
+        ws = _workspaces[key] = _zeros_before(dev, stream_handle, max(nbytes, 256))
+    return ws
+
+
+def _zeros_before(dev: torch.device, stream_handle: int, nbytes: int) -> torch.Tensor:
+    """nbytes zero bytes for the next kernel on the stream of this handle."""
+    make = lambda: torch.zeros(nbytes, dtype=torch.uint8, device=dev)  # noqa: E731
+    if dev.type != "cuda" or stream_handle == _stream(dev, None):
+        return make()
+    own, cur = _on(dev, stream_handle), torch.cuda.current_stream(dev)
+    own_captures, cur_captures = _capturing(dev, own), _capturing(dev, cur)
+    if cur_captures and not own_captures:
+        # a fill on the current stream would be recorded for the graph's replays and not run now
+        with torch.cuda.stream(own):
+            return make()
+    ws = make()  # on the current stream
+    # A captured stream may not wait for one outside its graph; such a fill runs
+    # now, the graph's first replay later.
+    if own_captures == cur_captures:
+        own.wait_stream(cur)
     return ws
 
 
