@@ -87,3 +87,16 @@ def test_schedules_keep_their_chunks():
         assert sched.kv_fetch in (0, 1, 2) and sched.state_rows > 0
         states = -(-sched.state_rows * H_Q * 128 * 4 // 256) * 256 + 2 * (-(-sched.state_rows * H_Q * 4 // 256) * 256)
         assert da.da_schedule_workspace_bytes(sched) == states + (1 << 20)
+
+
+def test_the_gpu_cases_reach_what_they_name():
+    from tests.dealt_cases import CASES, MOST_PIECES, PAGE_WINDOWS, PAGE_WINDOWS_CUS, deal
+    got = [deal(lens, H_Q, H_KV) for H_Q, H_KV, lens in CASES]
+    assert got[4]["per"] == 11 and got[4]["pieces"] == [26]
+    assert got[6]["passed"] >= 3 and got[7]["passed"] >= 3
+    assert {d["hpt"] for d in got} >= {1, 3, 8, 32}
+    H_Q, H_KV, lens = MOST_PIECES
+    assert deal(lens, H_Q, H_KV)["pieces"][1] == 64
+    for H_Q, H_KV, lens in PAGE_WINDOWS:
+        d = deal(lens, H_Q, H_KV, PAGE_WINDOWS_CUS)
+        assert d["pages"] > 64 and d["passed"] >= 2

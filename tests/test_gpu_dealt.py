@@ -11,27 +11,12 @@ import torch
 import paper_2604_00028_amd as da
 from oracle import decode_attention
 from workloads import custom_shape, make_inputs, paged_layout
+from tests.dealt_cases import CASES, MOST_PIECES, PAGE_WINDOWS, PAGE_WINDOWS_CUS, deal
 from tests.gpu_helpers import assert_parity, dev_inputs, say, to_dev, to_f64
 
 pytestmark = pytest.mark.gpu
 
 LSE_TOL = 1e-3
-
-CASES = [
-    (8, 1, [1]),                                          # one tile
-    (8, 1, [0, 0, 0]),                                    # nothing to read
-    (8, 1, [31, 32, 33, 0, 1, 64, 0]),                    # tile edges, empty sequences between
-    (64, 8, [512]),                                       # one sequence over many workgroups
-    (8, 1, [9000]),                                       # 64 pieces at most; page windows of 64 pages
-    (8, 1, [9000, 5, 0, 4100, 31]),                       # long and short in turn
-    (32, 4, [3000, 17, 0, 900, 2100, 64]),                # head, whole and tail pieces in one workgroup
-    (16, 2, [int(x) for x in np.random.default_rng(7).integers(0, 300, 200)]),   # several windows of 64 sequences
-    (16, 16, [700, 33, 1200]),                            # one head per KV head
-    (32, 1, [300, 40, 511, 2000]),                        # 32-head tiles (two column tiles, four waves)
-    (66, 2, [130, 700, 31]),                              # 33-head groups: three readers per KV head
-    (12, 4, [300, 95]),                                   # group of 3
-]
-
 
 def check(out, lse_t, O, lse, what):
     assert_parity(out, O, what)
@@ -176,3 +161,78 @@ def test_dealt_on_a_masked_stream():
             da.da_decode_attn_dealt(q, k, v, L, cu, out=out, workspace=ws)
     finally:
         destroy_stream(stream)
+
+
+def close(out, lse_t, O, lse, what):
+    """check(), and a relative error that a missed or doubled page would exceed (bf16 output: 1.7e-3)."""
+    check(out, lse_t, O, lse, what)
+    rel = float(np.linalg.norm(to_f64(out) - O) / np.linalg.norm(O))
+    assert rel <= 4e-3, f"{what}: {rel:.2e}"
+
+
+def test_dealt_most_pieces():
+    """A sequence in 64 pieces, the most the merge holds."""
+    H_Q, H_KV, lengths = MOST_PIECES
+    assert da.da_device_info()[0] != 256 or max(deal(lengths, H_Q, H_KV)["pieces"]) == 64
+    inp = make_inputs(custom_shape(2, H_Q, H_KV, max(lengths), varlen=True), seed=31, lengths=lengths)
+    O, lse = decode_attention(inp.q, inp.k, inp.v, inp.lengths, inp.cu_seqlens_k)
+    q, k, v, cu = dev_inputs(inp)
+    say("dealt 64 pieces")
+    lse_t = torch.empty(2, H_Q, dtype=torch.float32, device="cuda")
+    out = da.da_decode_attn_dealt(q, k, v, max(lengths), cu, lse_out=lse_t)
+    torch.cuda.synchronize()
+    close(out, lse_t, O, lse, "64 pieces")
+
+
+@pytest.mark.parametrize("H_Q,H_KV,lengths", PAGE_WINDOWS, ids=lambda x: str(x)[:24])
+def test_dealt_page_windows(H_Q, H_KV, lengths):
+    """Waves that pass more than the 64 page ids they hold at a time."""
+    from paper_2604_00028_amd.streams import cu_mask_stream, destroy_stream, split_masks
+    B, L = len(lengths), max(lengths)
+    inp = make_inputs(custom_shape(B, H_Q, H_KV, L, varlen=True), seed=37, lengths=lengths)
+    O, lse = decode_attention(inp.q, inp.k, inp.v, inp.lengths, inp.cu_seqlens_k)
+    pg = paged_layout(inp, 32, seed=6)
+    q, k, v = to_dev(inp.q), to_dev(pg.k_cache), to_dev(pg.v_cache)
+    bt, sl = torch.from_numpy(pg.block_table).cuda(), torch.from_numpy(pg.seq_lens).cuda()
+    stream, enabled = cu_mask_stream(split_masks(da.da_device_info()[0], 24)[1])
+    try:
+        assert enabled != PAGE_WINDOWS_CUS or deal(lengths, H_Q, H_KV, enabled)["pages"] > 64
+        lse_t = torch.empty(B, H_Q, dtype=torch.float32, device="cuda")
+        torch.cuda.synchronize()
+        say(f"dealt page windows {H_Q}/{H_KV} on {enabled} CUs")
+        out = da.da_decode_attn_dealt(q, k, v, L, block_table=bt, seq_lens=sl, lse_out=lse_t, stream=stream)
+        torch.cuda.synchronize()
+        close(out, lse_t, O, lse, f"page windows {H_Q}/{H_KV}")
+    finally:
+        destroy_stream(stream)
+
+
+@pytest.mark.parametrize("page", [None, 32])
+def test_dealt_lengths_and_pages_out_of_range(page):
+    """Lengths above L_K_max count as L_K_max and, paged, below 0 as 0; a
+    page id outside the cache reads as zero keys and values."""
+    H_Q, H_KV, lengths, L = 16, 2, [1000, 700, 350, 600], 640
+    inp = make_inputs(custom_shape(4, H_Q, H_KV, 1000, varlen=True), seed=41, lengths=lengths)
+    cuh = inp.cu_seqlens_k
+    q, k, v, cu = dev_inputs(inp)
+    kw = dict(cu_seqlens_k=cu)
+    keep = [L, L, 350, 600]
+    kn, vn = inp.k.copy(), inp.v.copy()
+    if page is not None:
+        pg = paged_layout(inp, page, seed=9)
+        for b, j, bad in ((0, 3, -1), (2, 0, pg.k_cache.shape[0]), (3, 18, 2**31 - 1)):
+            pg.block_table[b, j] = bad
+            rows = slice(cuh[b] + page * j, min(cuh[b] + page * (j + 1), cuh[b + 1]))
+            kn[rows], vn[rows] = 0, 0
+        pg.seq_lens[1] = -5
+        keep[1] = 0
+        k, v = to_dev(pg.k_cache), to_dev(pg.v_cache)
+        kw = dict(block_table=torch.from_numpy(pg.block_table).cuda(), seq_lens=torch.from_numpy(pg.seq_lens).cuda())
+    cut = np.concatenate([np.arange(cuh[b], cuh[b] + n) for b, n in enumerate(keep)])
+    O, lse = decode_attention(inp.q, kn[cut], vn[cut], np.array(keep, dtype=np.int64),
+                              np.concatenate([[0], np.cumsum(keep)]).astype(np.int32))
+    say(f"dealt out of range page={page}")
+    lse_t = torch.empty(4, H_Q, dtype=torch.float32, device="cuda")
+    out = da.da_decode_attn_dealt(q, k, v, L, lse_out=lse_t, **kw)
+    torch.cuda.synchronize()
+    close(out, lse_t, O, lse, f"out of range page={page}")
