@@ -482,18 +482,19 @@ struct TileReducer {
   // Q^T as the MFMA B operand.  The reduction index of the product may
   // map to head dims in any order as long as K and Q agree: k-step j,
   // lane group `quad` covers dims [32j + 8*quad, +8).  The lane holds those
-  // dims of head column `col` (zeros for padding) of the hpt rows at qrow.
+  // dims of head column `col` of the hpt rows at qrow; rows past them are out
+  // of the buffer's range and read as zeros.  (Loads under a lane guard made
+  // the compiler wait for Q before the first K/V load: launches of many short
+  // chunks up to 7% slower.)
   __device__ __forceinline__ void load_q(const uint16_t* qrow, int hpt, int col) {
+    const __amdgpu_buffer_rsrc_t qr = make_rsrc(qrow, (uint32_t)hpt * (D * 2));
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const int h = nt * 16 + col;
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        u32x4 x = {0u, 0u, 0u, 0u};
-        if (h < hpt) x = *reinterpret_cast<const u32x4*>(qrow + (int64_t)h * D + 32 * j + 8 * quad);
-        q[nt][j] = as_bf16x8(x);
-      }
-    }
+      for (int j = 0; j < 4; ++j)
+        q[nt][j] = as_bf16x8(__builtin_bit_cast(
+            u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                       qr, (uint32_t)(nt * 16 + col) * (D * 2) + 64u * j + 16u * quad, 0, 0)));
   }
 
   __device__ __forceinline__ void reset() {
