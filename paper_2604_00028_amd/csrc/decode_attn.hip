@@ -453,15 +453,19 @@ __device__ __forceinline__ void merge_tile(const Params& p, float* lds, int64_t 
   // Up to R rows need one column item per thread, which leaves registers for
   // 16 chunks at once: B=1, H_KV=8, L_K=8192 in 16 chunks 12.0 -> 11.4 us per
   // call against batches of 8.  Loads past the last chunk still take their
-  // turn and their code (4 chunks in a batch of 16: the step of 80 layers at
-  // L_K=512 515 -> 557 us; in a batch of 4, 507), so few chunks take a small
-  // batch, and more than 16, whose batches follow each other, the middle one.
+  // turn and their code (4 chunks in a batch of 16: 8% of the step of 80 layers
+  // at L_K=512), so few chunks take a small batch, and more than 16, whose
+  // batches follow each other, the middle one.  2-4 chunks of 9 to 16 heads in
+  // a batch of 8 ran at 0.96-0.98x of a loop over the chunks there are, in a
+  // batch of 4 at 1.04-1.07x (5-8 chunks of up to 8 heads in one of 8: 0.97-1.02x).
   if (p.hpt <= R && s <= 4)
     merge_columns<W, 1, 4, FIRST>(p, lds, srow0, cstride, s, orow0, tid, first_rows);
   else if (p.hpt <= R && (s <= 8 || s > 16))
     merge_columns<W, 1, 8, FIRST>(p, lds, srow0, cstride, s, orow0, tid, first_rows);
   else if (p.hpt <= R)
     merge_columns<W, 1, 16, FIRST>(p, lds, srow0, cstride, s, orow0, tid, first_rows);
+  else if (IPT == 2 && s <= 4)
+    merge_columns<W, 2, 4, FIRST>(p, lds, srow0, cstride, s, orow0, tid, first_rows);
   else if (IPT > 2 && p.hpt <= 2 * R)
     merge_columns<W, 2, 8, FIRST>(p, lds, srow0, cstride, s, orow0, tid, first_rows);
   else

@@ -128,6 +128,23 @@ def test_fused_counters_return_to_zero_and_workspace_is_shared():
         assert int(region.abs().sum()) == 0, "arrival counters not reset"
 
 
+@pytest.mark.parametrize("hpt", [1, 8, 9, 12, 16, 17, 24, 32])
+def test_fused_merge_batches(hpt):
+    """Either side of every line of the merge's batches: tiles of 8, 16 and
+    32 heads, 4, 8 and 16 chunks; the two-launch merge's bits."""
+    B, L = 2, 2100
+    inp = make_inputs(custom_shape(B, hpt, 1, L), seed=hpt)
+    O, lse = decode_attention(inp.q, inp.k, inp.v)
+    q, k, v, cu = dev_inputs(inp)
+    for s in (2, 4, 5, 8, 9, 16, 17, 64):
+        say(f"merge batches hpt={hpt} s={s}")
+        fused = edited(da.da_make_plan(B, hpt, 1, L, num_splits=s, pack_gqa=1), combine=1)
+        assert fused.heads_per_tile == hpt or hpt > 16
+        one = run_plan(q, k, v, cu, L, fused)
+        check(*one, O, lse, f"merge batches hpt={hpt} s={s}")
+        assert same_bits(one, run_plan(q, k, v, cu, L, edited(fused, combine=0))), f"hpt={hpt} s={s}"
+
+
 @pytest.mark.parametrize("s", [3, 16])
 def test_fused_repeats_and_graph_replay(s):
     sh = config_shapes(2)[3]
