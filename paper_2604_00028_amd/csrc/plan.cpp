@@ -829,11 +829,13 @@ bool prefers_dealt(int B, int H_Q, int H_KV, int L_K_max, int64_t keys, int cus)
   // shapes, equal, uniform, lognormal and bimodal lengths, packed and paged),
   // each with other batches in turn and over and over: with these lines 156 of
   // narrow tiles are taken, 1.72x faster in turn and 1.83x over and over, one
-  // of them slower (0.90x); from 60 tiles on 9 of 194 are, down to 0.77x.
-  // Lines on the share alone took equal lengths at 0.84-0.98x.  Wide tiles
-  // lose up to a difference of 270 tiles (0.86x) and gain on all 7 batches
-  // past 300 (1.32x and more).
-  return longest >= 1.7 * share && longest - share >= (wide ? 320.0 : 80.0);
+  // of them slower (0.90x); from 60 tiles on 9 of 194 are, down to 0.77x.  Of
+  // 220 drawn afterwards 45 are taken, 1.77x and 1.79x, none slower (bench.py
+  // --mixed-sweep).  Lines on the share alone took equal lengths at
+  // 0.84-0.98x.  Wide tiles lose up to a difference of 270 tiles (0.86x) and
+  // beyond it at a ratio of 1.9 (0.95x); all 6 past 300 tiles and a ratio of 3
+  // gain 1.32x and more.
+  return wide ? longest >= 3.0 * share && longest - share >= 320.0 : longest >= 1.7 * share && longest - share >= 80.0;
 }
 
 WorkspaceLayout workspace_layout(int B, int H_Q, int d, int s) {

@@ -24,8 +24,9 @@ def test_preferred_where_the_longest_chunk_exceeds_the_share():
     # the lines: 80 tiles over a share of 6.25, and 1.7 shares of 200 tiles
     assert next(t for t in range(1, 4000) if p(100, 64, 8, 32 * t, 3200)) == 87
     assert next(t for t in range(1, 4000) if p(32, 64, 8, 32 * t, 32 * 6368)) == 340
-    # wide head tiles need four times the difference
+    # wide head tiles need four times the difference and 3 shares
     assert next(t for t in range(1, 4000) if p(64, 128, 2, 32 * t, 32 * 6336)) == 420
+    assert next(t for t in range(1, 4000) if p(64, 128, 2, 32 * t, 32 * 12736)) == 600
     # what the Python entry points assume without asking
     assert p(129, 8, 1, bnd.DEALT_MIN_KEYS, 1) and not p(129, 8, 1, bnd.DEALT_MIN_KEYS - 1, 1)
     # head tiles that leave more than a tenth of the CUs idle, or more than the arrival counters
