@@ -34,6 +34,7 @@ import contextlib
 import gc
 import hashlib
 import json
+import math
 import os
 import statistics
 import sys
@@ -104,6 +105,11 @@ def parse():
                          "on mixed-length batches and write the results to OUT_JSON")
     ap.add_argument("--schedule-sweep-summary", metavar="IN_JSON", default=None,
                     help="summarise a --schedule-sweep result into profiles/schedule_mixed_length_batches.md")
+    ap.add_argument("--mixed-sweep", metavar="OUT_JSON", default=None,
+                    help="time the dealt launch against the launch with one split count on batches of mixed and "
+                         "equal lengths and write the results to OUT_JSON")
+    ap.add_argument("--mixed-sweep-summary", metavar="IN_JSON", default=None,
+                    help="summarise a --mixed-sweep result into profiles/dealt_route_mixed_batches.md")
     ap.add_argument("--waves-sweep", metavar="OUT_JSON", default=None,
                     help="time one-split launches of two waves per workgroup against four on shapes of 192-1024 "
                          "workgroups (the planner's own wave count and the other one) and write OUT_JSON")
@@ -598,6 +604,118 @@ def schedule_sweep_summary(path: str) -> None:
     with open(PROFILE_SCHEDULE, "w") as f:
         f.write("\n".join(lines) + "\n")
     print("\n".join(lines))
+
+
+PROFILE_MIXED = os.path.join(ROOT, "profiles", "dealt_route_mixed_batches.md")
+MIXED_BATCHES = (220, 2711)    # batches, seed
+MIXED_LINES = ((60, 1.4), (60, 1.7), (80, 1.4), (80, 1.7), (80, 2.0), (100, 1.7), (150, 1.7))  # tiles, ratio
+
+
+def mixed_sweep_run(args, da, torch, np) -> None:
+    """For every batch of workloads.mixed_batches: the dealt launch and the
+    launch with one split count, each with enough K/V copies in turn that none
+    stays cached, and over one copy again and again."""
+    from workloads import mixed_batches
+    rows = []
+    cus = da.da_device_info()[0]
+    for n, (lens, H_Q, H_KV, page) in enumerate(mixed_batches(*MIXED_BATCHES)):
+        B, tot, L = len(lens), sum(lens), max(lens)
+        need = da.da_dealt_workspace_bytes(B, H_Q, H_KV)
+        if not need:
+            continue
+        log(f"mixed sweep {n}: B={B} {H_Q}/{H_KV} page={page}")
+        gen = torch.Generator(device="cuda").manual_seed(n)
+        kv_bytes = tot * H_KV * 512
+        copies = max(2, min(16, -(-(640 << 20) // kv_bytes)))
+        new = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)  # noqa: E731
+        q, out = new(B, H_Q, 128), torch.empty(B, H_Q, 128, dtype=torch.bfloat16, device="cuda")
+        starts = np.concatenate([[0], np.cumsum(lens)])
+        kvs = [(new(tot, H_KV, 128), new(tot, H_KV, 128)) for _ in range(copies)]
+        orc = OracleVarlen(np, torch, q, *kvs[0], lens, sorted({0, lens.index(L)}))
+        if page is None:
+            cu, pool = torch.from_numpy(starts.astype(np.int32)).cuda(), tot
+            own = lambda i, c, ws: da.da_decode_attn(q, *kvs[i % c], cu, out=out, L_K_max=L, workspace=ws)  # noqa: E731
+            deal = lambda i, c, ws: da.da_decode_attn_dealt(q, *kvs[i % c], L, cu, out=out, workspace=ws)  # noqa: E731
+        else:
+            pages = [-(-x // page) for x in lens]
+            order = torch.randperm(sum(pages), generator=torch.Generator().manual_seed(n))
+            table, pool, at = torch.zeros(B, max(pages), dtype=torch.int32), sum(pages) * page, 0
+            for b, m in enumerate(pages):
+                table[b, :m] = order[at:at + m].to(torch.int32)
+                at += m
+
+            def paged(x):
+                y = torch.zeros(pool, H_KV, 128, dtype=torch.bfloat16, device="cuda")
+                for b, m in enumerate(pages):
+                    key = torch.arange(lens[b])
+                    y[(table[b].long()[key // page] * page + key % page).cuda()] = x[int(starts[b]):int(starts[b + 1])]
+                return y.view(-1, page, H_KV, 128)
+
+            kvs = [(paged(a), paged(b)) for a, b in kvs]
+            bt, sl = table.cuda(), torch.tensor(lens, dtype=torch.int32, device="cuda")
+            own = lambda i, c, ws: da.da_decode_attn_paged(q, *kvs[i % c], bt, sl, L, out=out, workspace=ws)  # noqa: E731
+            deal = lambda i, c, ws: da.da_decode_attn_dealt(  # noqa: E731
+                q, *kvs[i % c], L, block_table=bt, seq_lens=sl, out=out, workspace=ws)
+        ws = torch.zeros(max(need, da.da_workspace_bytes(B, H_Q, 128, 64)), dtype=torch.uint8, device="cuda")
+        steps = max(copies, 8 if kv_bytes > (256 << 20) else 24 if kv_bytes > (32 << 20) else 100)
+        row = {"B": B, "H_Q": H_Q, "H_KV": H_KV, "page": page, "keys": tot, "longest": L, "mb": round(kv_bytes / 1e6)}
+        for what, c in (("turn", copies), ("repeat", 1)):
+            vs = [Timed(torch, lambda i, f=f: f(i, c, ws), steps, out, name) for name, f in (("one", own), ("dealt", deal))]
+            validate(torch, orc, vs, f"mixed sweep {n}")
+            interleave(torch, vs, 5)
+            row[what] = [round(v.median, 2) for v in vs]
+        heads = heads_per_tile(H_Q, H_KV, 32)
+        groups, tiles = cus // (H_Q // heads), -(-L // 32)
+        row["wide"] = heads > 16
+        row["share"] = min(pool // 32 + B, B * tiles) / groups
+        row["chunk"] = tiles / max(1, cus // (B * (H_Q // heads)))
+        row["taken"] = bool(da.da_prefers_dealt(B, H_Q, H_KV, L, pool))
+        rows.append(row)
+        del kvs, vs
+    with open(args.mixed_sweep, "w") as f:
+        json.dump({"device_cus": cus, "kernel_source_sha256": kernel_source_sha(), "validated": VALIDATION["validated"],
+                   "invalid": VALIDATION["invalid"], "rows": rows}, f)
+    log(f"wrote {args.mixed_sweep}")
+
+
+def mixed_sweep_summary(path: str) -> None:
+    d = json.load(open(path))
+    gain = lambda r, what: r[what][0] / r[what][1]  # noqa: E731
+    least = lambda r: min(gain(r, "turn"), gain(r, "repeat"))  # noqa: E731
+    mean = lambda v: math.exp(sum(map(math.log, v)) / len(v)) if v else 1.0  # noqa: E731
+    lines = ["# Where the dealt launch pays (MI355X)", "",
+             "Made by `python bench.py --mixed-sweep mixed.json` then `python bench.py --mixed-sweep-summary "
+             f"mixed.json`: {len(d['rows'])} batches (`workloads.mixed_batches{MIXED_BATCHES}`), each output checked "
+             f"against the oracle ({d['validated']} launches, {len(d['invalid'])} invalid).  Times are those of the "
+             "launch with one split count over those of the dealt launch, HIP-graph replay, medians of 5: with "
+             "640 MB of batches in turn, and one batch over and over.  `excess`: the longest chunk of one split "
+             "count less the even share, in 32-key tiles; `ratio`: the one over the other.  A batch counts as "
+             "slower below 0.985x in either.", "",
+             "| batches with | taken | turn | repeat | slower | worst |", "|---|---|---|---|---|---|"]
+
+    def line(name, rows):
+        lines.append(f"| {name} | {len(rows)} | {mean([gain(r, 'turn') for r in rows]):.2f}x | "
+                     f"{mean([gain(r, 'repeat') for r in rows]):.2f}x | {sum(least(r) < 0.985 for r in rows)} | "
+                     f"{min(map(least, rows), default=1.0):.3f}x |")
+
+    rows, taken = d["rows"], [r for r in d["rows"] if r["taken"]]
+    line("the library's lines (`da_prefers_dealt`)", taken)
+    line("all", rows)
+    for wide in (False, True):
+        for excess, ratio in MIXED_LINES + (((320, 1.7), (320, 3.0)) if wide else ()):
+            line(f"{'wide' if wide else 'narrow'} head tiles, excess >= {excess}, ratio >= {ratio}",
+                 [r for r in rows if r["wide"] == wide and r["chunk"] - r["share"] >= excess
+                  and r["chunk"] >= ratio * r["share"]])
+    lines += ["", "Every batch taken, slowest first:", "",
+              "| B | heads | page | keys | longest | MB | share | excess | turn us | repeat us | turn | repeat |",
+              "|---|---|---|---|---|---|---|---|---|---|---|---|"]
+    for r in sorted(taken, key=least):
+        lines.append(f"| {r['B']} | {r['H_Q']}/{r['H_KV']} | {r['page'] or '-'} | {r['keys']} | {r['longest']} | {r['mb']} "
+                     f"| {r['share']:.0f} | {r['chunk'] - r['share']:.0f} | {r['turn'][0]} -> {r['turn'][1]} | "
+                     f"{r['repeat'][0]} -> {r['repeat'][1]} | {gain(r, 'turn'):.2f}x | {gain(r, 'repeat'):.2f}x |")
+    with open(PROFILE_MIXED, "w") as f:
+        f.write("\n".join(lines) + "\n")
+    print("\n".join(lines[:28]))
 
 
 def cu_margin_run(args, da, torch, np) -> dict:
@@ -1460,6 +1578,9 @@ def main():
     if args.occupancy_summary:
         occupancy_summary(args.occupancy_summary)
         return
+    if args.mixed_sweep_summary:
+        mixed_sweep_summary(args.mixed_sweep_summary)
+        return
     if args.schedule_sweep_summary:
         schedule_sweep_summary(args.schedule_sweep_summary)
         return
@@ -1487,6 +1608,9 @@ def main():
         return
     if args.regression:
         regression_run(args, da, torch)
+        return
+    if args.mixed_sweep:
+        mixed_sweep_run(args, da, torch, np)
         return
     if args.schedule_sweep:
         schedule_sweep_run(args, da, torch, np)

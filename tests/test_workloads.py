@@ -60,3 +60,15 @@ def test_split_masks_keep_cus_on_every_xcd():
     for bad in (0, 4, 32):
         with pytest.raises(ValueError):
             split_masks(256, bad)
+
+
+def test_mixed_batches():
+    from workloads import mixed_batches
+    batches = mixed_batches(40, 1)
+    assert batches == mixed_batches(40, 1) and batches != mixed_batches(40, 2)
+    for lens, H_Q, H_KV, page in batches:
+        assert 1 <= len(lens) <= 128 and 1 <= min(lens) and max(lens) <= 32768 and H_Q % H_KV == 0
+        assert page is None or page % 32 == 0
+        assert 1 << 25 <= sum(lens) * H_KV * 512 <= 1 << 30
+    assert {p is None for *_, p in batches} == {True, False}
+    assert any(len(set(b[0])) == 1 for b in batches) and any(max(b[0]) > 16 * min(b[0]) for b in batches)

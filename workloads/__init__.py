@@ -300,6 +300,36 @@ def schedule_batches(kind: str) -> List[tuple]:
     raise ValueError(kind)
 
 
+def mixed_batches(n: int, seed: int) -> List[tuple]:
+    """n batches of 1-128 sequences of up to 32768 keys for measuring where the
+    dealt launch pays: equal, uniform, lognormal and bimodal lengths, 11 head
+    shapes, at most 1 GiB of K/V and at least 8 tiles per CU.  (lengths, H_Q,
+    H_KV, page size or None for packed K/V)."""
+    heads = [(8, 1), (32, 1), (16, 2), (32, 2), (128, 2), (32, 4), (64, 4), (64, 8), (40, 8), (128, 16), (16, 16)]
+    rng = np.random.default_rng(seed)
+    log_int = lambda lo, hi: int(round(float(np.exp(rng.uniform(np.log(lo), np.log(hi))))))  # noqa: E731
+    out = []
+    while len(out) < n:
+        H_Q, H_KV = heads[int(rng.integers(len(heads)))]
+        B, hi = log_int(1, 128), log_int(768, 32768)
+        lo = [1, 16, max(1, hi // 16), hi // 2][int(rng.integers(4))]
+        kind = ["equal", "uniform", "lognormal", "bimodal"][int(rng.integers(4))]
+        page = [None, None, 32, 64, 128, 256][int(rng.integers(6))]
+        if kind == "equal":
+            x = np.full(B, hi)
+        elif kind == "uniform":
+            x = rng.integers(lo, hi + 1, B)
+        elif kind == "lognormal":
+            x = np.clip(rng.lognormal(np.log(max(lo, hi / 16)), 1.0, B), lo, hi)
+        else:  # one sequence in eight at the full length
+            x = np.where(rng.permutation(B) < max(1, B // 8), hi, max(lo, hi // 32))
+        lens = [int(v) for v in x]
+        kv = sum(lens) * H_KV * HEAD_DIM * 4
+        if 8 * 256 * 32 * HEAD_DIM * 4 <= kv <= 1 << 30:
+            out.append((lens, H_Q, H_KV, page))
+    return out
+
+
 def algorithmic_bytes(B: int, H_Q: int, H_KV: int, total_keys: int, D: int = HEAD_DIM,
                       varlen: bool = False) -> int:
     """Bytes the method must move once: K and V once, Q read, O written (bf16),
