@@ -983,13 +983,9 @@ TRAFFIC_WORKLOADS = {"headline": "llama70b_gqa_b1_l512", "highload": "highload_b
                      "ragged": "ragged_highload_b32_h64_kv8"}
 
 
-# A decode call's main launch: the split kernel, or the even deal of a long mixed batch.
-DECODE_KERNELS = ("void (anonymous namespace)::split_partial_kernel", "void (anonymous namespace)::dealt_kernel")
-
-
-def counter_avg(path: str, kernel_prefix, counter: str) -> float:
+def counter_avg(path: str, kernel_prefix: str, counter: str) -> float:
     """Mean per-dispatch value (KiB) of one counter for kernels whose name
-    starts with kernel_prefix (or one of several), from a rocprofv3 counter_collection.csv."""
+    starts with kernel_prefix, from a rocprofv3 counter_collection.csv."""
     import csv
     vals = [float(r["Counter_Value"]) for r in csv.DictReader(open(path))
             if r["Kernel_Name"].startswith(kernel_prefix) and r["Counter_Name"] == counter]
@@ -1011,8 +1007,8 @@ def traffic_summary(d: str) -> None:
                       "-- python3 bench.py --only <w> --steps 20 --rounds 1 --highload-steps 3",
            "workloads": {}}
     for w, name in TRAFFIC_WORKLOADS.items():
-        fk = counter_avg(f("FETCH_SIZE", w), DECODE_KERNELS, "FETCH_SIZE")
-        wk = counter_avg(f("WRITE_SIZE", w), DECODE_KERNELS, "WRITE_SIZE")
+        fk = counter_avg(f("FETCH_SIZE", w), "void (anonymous namespace)::split_partial_kernel", "FETCH_SIZE")
+        wk = counter_avg(f("WRITE_SIZE", w), "void (anonymous namespace)::split_partial_kernel", "WRITE_SIZE")
         out["workloads"][name] = {"fetch_kib_counter": round(fk, 2), "write_kib_counter": round(wk, 2),
                                   "fetch_bytes": int(fk * 1024 * fetch_scale), "write_bytes": int(wk * 1024 * write_scale)}
     with open(PROFILE_TRAFFIC, "w") as fh:

@@ -41,9 +41,9 @@
 //  * K/V loads are raw buffer loads whose record count ends at the wave's
 //    last key: keys past it read as zeros without touching memory, so ragged
 //    tails cost no traffic and no load needs a mask or a branch.
-//  * Batches of mixed lengths whose keys fill the chip take the dealt launch
-//    instead (dealt_kernel): the batch's tiles are shared evenly among the
-//    CUs, across sequence ends.
+//  * Batches of mixed lengths whose longest sequence would hold up the launch
+//    have the dealt launch instead (dealt_kernel): the batch's tiles are
+//    shared evenly among the CUs, across sequence ends.
 //  * With packing off, workgroup ids are remapped so consecutive tiles land
 //    on the same XCD (dispatch is round-robin over the 8 XCDs): the query
 //    heads of one KV head then share that XCD's L2.  With packing on, each
@@ -1272,11 +1272,12 @@ constexpr int dealt_smem_bytes(int W, int NT) {
 // Bound by HBM: 32 sequences of 1024 to 16384 keys over 8 KV heads (1.06
 // GB) 234 -> 164 us against one split for all (6.4 TB/s; workgroups end
 // within 8% of each other, which is what is lost against equal lengths: 32 of
-// 8192 keys take 150.5 us, 7.1 TB/s), 64 sequences of 140 to 22365 keys over
+// 8192 keys take 150.5 us, 7.1 TB/s; 160-164 by the box), 64 sequences of 140 to 22365 keys over
 // 4 KV heads in 64-key pages (0.5 GB) 258 -> 88 us.  Four waves measured
 // 1-4% slower, three 1-4%, two workgroups a CU 1-9%.  The fixed part is about 8 us, of
-// it 2-4 for the merge, so short batches stay with one split count
-// (prefers_dealt), and no workgroup takes fewer tiles than about the square
+// it 2-4 for the merge, and passing from one sequence to the next costs three
+// or four tiles, so batches that one split count cuts evenly enough stay with
+// it (prefers_dealt), and no workgroup takes fewer tiles than about the square
 // root of the longest sequence's: fewer, longer pieces, whose merge is
 // cheaper, cost no more than the stream saves.
 template <int NT, int W, bool PG, bool NTL>
